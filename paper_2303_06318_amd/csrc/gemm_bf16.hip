@@ -1,45 +1,54 @@
-// Grouped bf16 GEMM on gfx950 matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulation) for the
+// Grouped bf16 GEMM on gfx950 matrix cores (v_mfma_f32_16x16x32_bf16, fp32 accumulation) for the
 // expert FFN: forward (Z = D W1 with fused GeLU and GeLU', Y = H W2), data gradients (dH = dY W2^T
 // times the saved GeLU', dD = dZ W1^T) and weight gradients (dW = A^T B over the kept rows).
 //
 // One workgroup of 512 threads (8 waves, 2 x 4) owns a 256 x 256 output tile of one expert and
-// walks K in 32-deep tiles through four 32 KB LDS stages (three tiles, 96 KB, in flight).  Each
-// wave owns 128 x 64 of the tile: 4 x 2 MFMA blocks of 32 x 32.  Global data goes straight into
+// walks K in 64-deep tiles through two to three LDS stages (156 KB).  Each wave owns 64 columns, and 64 rows
+// in either 128-row half of the tile: 8 x 4 MFMA blocks of 16 x 16.  Global data goes straight into
 // LDS (buffer_load ... lds, 16 bytes per lane, no register staging); out-of-range lanes deliver
 // zeros, so ragged row counts and K tails need no branches.  The two waves of a SIMD alternate
 // between a memory phase and an MFMA phase, half an iteration apart (see the main loop).
 //
+// The kernel runs into the chip's power limit (the shader clock sinks from 2.4 to 1.7-1.9 GHz), so what
+// counts is energy per flop.  Registers-only loops on random operands sustain 2.11 PFLOP/s with the
+// 16 x 16 x 32 instruction and 1.87 with 32 x 32 x 16: per multiply-add it reads and writes half as many
+// accumulators.
+//
 // Operands are taken in the layout the layer stores them in, so no transposed copy is ever made:
 //   "KC" operand: the reduction index is contiguous in memory  -> LDS tile [256 x][64 k], 16-byte
 //                 LDS reads deliver 8 consecutive k to a lane directly;
-//   "XC" operand: the output index is contiguous in memory     -> LDS tile [64 k][256 x], read with
+//   "XC" operand: the output index is contiguous in memory     -> LDS tile [64 k][x], read with
 //                 the LDS transpose load (ds_read_b64_tr_b16), which hands lane i of a 16-lane
 //                 group the i-th column of a 4 x 16 block.
+// The k-tile is 64 deep because 64 k are 128 bytes of a KC row, one cache line: with 32-deep tiles
+// every line was brought from L2 into the CU twice, once for each half (counted: 67 M line reads
+// per launch with two KC operands, 50 M with one, against 33.5 M with none).
+//
 // A direct-to-LDS load writes lane L's 16 bytes at base + 16 L, so tiles cannot be padded; bank
 // conflicts are avoided by XOR-swizzling the 16-byte granules inside each row instead:
 //   KC: granule g of row r sits at position g ^ ((r >> 1) & 7)   (rows are 128 bytes)
-//   XC: granule g of k-row k sits at position g ^ ((k & 3) << 2) (k-rows are 512 bytes)
+//   XC: granule g of k-row k sits at position g ^ ((k & 3) << 2) ^ ((k >> 3 & 1) << 1) (k-rows are 256 bytes
+//       for A, whose two 128-column halves are separate, and 512 bytes for B)
 // Rows beyond kept[e] are never read (loaded as zero) and never written.
 #include <type_traits>
 #include "moe_common.h"
 
 namespace moe {
 
-constexpr int BM = 256, BN = 256, BK = 32, GEMM_THREADS = 512;
-constexpr int KS = BK / 16;                    // MFMA k-steps per k-tile
-constexpr int CPW = BK / 16;                   // 1 KB chunks per wave, operand and k-tile
+constexpr int BM = 256, BN = 256, BK = 64, GEMM_THREADS = 512;
+constexpr int KS = BK / 32;                    // MFMA k-steps per k-tile
 constexpr int KC_ROW = BK * 2;                 // bytes of one KC row in LDS
-constexpr int KC_G = BK / 8;                   // 16-byte granules per KC row
-constexpr int KC_SWZ_SHIFT = 2;                // rows per 256 bytes
 constexpr int LIGHT_BLOCKS = 4;                // an expert with at most this many 32-row blocks is one "light" tile
 constexpr int MAXB = 9;                        // 32-row blocks of a tile when A is a KC operand: 8, or 9 in a "tall" tile
-constexpr int A_ROWS = MAXB * 32;              // rows of the A stage and of the epilogue staging tile
-constexpr int NSTAGE = 4;                      // LDS stages; tiles are requested NSTAGE-1 k-tiles ahead
-constexpr int OPER_BYTES = 256 * BK * 2;       // 256 rows or columns of one operand's k-tile (16 KB)
-constexpr int OPER_A_BYTES = A_ROWS * BK * 2;  // A's part of a stage: room for the ninth block of a tall tile (18 KB)
-constexpr int STAGE_BYTES = OPER_A_BYTES + OPER_BYTES;
+constexpr int A_ROWS = MAXB * 32;              // rows of the epilogue staging tile
+constexpr int HALF_BYTES = 128 * BK * 2;       // one 128-row (or 128-column) half of A's k-tile (16 KB)
+constexpr int X_BYTES = 32 * BK * 2;           // the ninth block of a tall tile (4 KB)
+constexpr int B_BYTES = 256 * BK * 2;          // B's k-tile (32 KB)
+// LDS map: A's lower half (three stages), upper half (two), ninth block (three), B (two); the stages of a part
+// lie next to each other, so that a read's stage is an immediate offset where it is known at compile time
+constexpr int A_HI = 0, A_LO = 2 * HALF_BYTES, A_X = A_LO + 3 * HALF_BYTES, B_AT = A_X + 3 * X_BYTES;
 constexpr int CLD = BN + 8;                    // epilogue staging row (elements)
-constexpr int SMEM_BYTES = A_ROWS * CLD * 2 > NSTAGE * STAGE_BYTES ? A_ROWS * CLD * 2 : NSTAGE * STAGE_BYTES;
+constexpr int SMEM_BYTES = A_ROWS * CLD * 2 > B_AT + 2 * B_BYTES ? A_ROWS * CLD * 2 : B_AT + 2 * B_BYTES;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -99,24 +108,16 @@ __device__ __forceinline__ i32x4 make_rsrc(const void *p, uint32_t bytes) {
 }
 constexpr uint32_t OOB = 0x80000000u;
 
-// One direct global -> LDS load: lane L's 16 bytes land at LDS byte address lds_addr + 16 L.
+// One direct global -> LDS load: lane L's 16 bytes land at LDS byte address lds_addr + 16 L, taken from
+// voff (per lane) + soff (same for all lanes).
 // Written as inline assembly so that the compiler does not order later LDS reads of the *other*
 // stage behind it; completion is awaited explicitly (s_waitcnt vmcnt) before the stage is read.
-__device__ __forceinline__ void load_to_lds(const i32x4 &rsrc, uint32_t lds_addr, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+__device__ __forceinline__ void load_to_lds(const i32x4 &rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :
-                 : "s"(lds_addr), "v"(voff), "s"(rsrc)
+                 : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
                  : "memory", "m0");
 }
-
-// Per-thread state of the global -> LDS copy of one operand.  A wave copies CPW consecutive chunks
-// of the tile's one-KB chunks; lane L fills granule L of the chunk.
-//   KC chunk: 1024 / KC_ROW rows, lane L -> row L / KC_G, position L % KC_G
-//   XC chunk: 2 k-rows x 512 bytes, lane L -> k-row L/32, position L%32
-struct Loader {
-    uint32_t off[CPW];    // byte offset of this lane's granule at k-tile 0 (OOB if outside the operand in x)
-    int32_t kthr[CPW];    // the granule is inside K for k-tile origin k0 iff k0 < kthr
-};
 
 // Where row gx of a KC operand lives in the array its resource covers, when that is not row gx itself:
 // through an index array (negative entry: no such row), or in the row shares of duplicate token dropping
@@ -130,65 +131,84 @@ struct RowMap {
     }
 };
 
-template <bool XC>
-__device__ __forceinline__ void loader_init(Loader &L, int ld, int x0, int xlim, int klim, int wave, int lane,
-                                            const RowMap &map = RowMap{nullptr, 0, 0, 0}) {
-#pragma unroll
-    for (int q = 0; q < CPW; ++q) {
-        const int chunk = wave * CPW + q;
+// Global -> LDS copy of one operand.  A part of a tile (a half of A, the whole of B) is filled by 1 KB
+// chunks, chunk wave + 8 q by wave `wave`; lane L fills granule L of the chunk:
+//   KC chunk:   8 rows of 128 bytes,    lane L -> row L / 8,    position L % 8
+//   XC A chunk: 4 k-rows of 256 bytes,  lane L -> k-row L / 16, position L % 16
+//   XC B chunk: 2 k-rows of 512 bytes,  lane L -> k-row L / 32, position L % 32
+// Chunks of a wave are 8 apart, so the swizzle of a lane is the same in all of them, and in an XC operand
+// they differ by a whole number of k-rows, which goes into the load's scalar offset: one offset register
+// per part, whereas the rows of a KC operand are bounds-checked (or gathered) one by one.
+template <bool XC, int NQ, int XC_COLS>
+struct Loader {
+    static constexpr int KROWS = 1024 / (XC_COLS * 2);      // XC: k-rows per chunk
+    uint32_t off[XC ? 1 : NQ];           // byte offset of this lane's granule at k = 0 (OOB: outside the operand in x)
+    int32_t kthr;                        // the granule of chunk q is below klim iff k0 (XC: + q * 8 * KROWS) < kthr
+    __device__ __forceinline__ void init_k(int klim, int wave, int lane) {
+        if (XC) kthr = klim - (wave * KROWS + lane / (64 / KROWS));
+        else kthr = klim - (((lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7)) << 3);
+    }
+    __device__ __forceinline__ void init(int ld, int x0, int xlim, int wave, int lane,
+                                         const RowMap &map = RowMap{nullptr, 0, 0, 0}) {
         if (XC) {
-            const int krow = chunk * 2 + (lane >> 5);
-            const int g = (lane & 31) ^ ((krow & 3) << 2);
-            const int gx = x0 + g * 8;
-            L.off[q] = gx < xlim ? ((uint32_t)krow * ld + gx) * 2u : OOB;
-            L.kthr[q] = klim - krow;
+            const int krow = wave * KROWS + lane / (64 / KROWS);
+            const int gx = x0 + (((lane % (64 / KROWS)) ^ ((krow & 3) << 2) ^ ((krow >> 3 & 1) << 1)) << 3);
+            off[0] = gx < xlim ? ((uint32_t)krow * ld + gx) * 2u : OOB;
         } else {
-            const int row = chunk * (1024 / KC_ROW) + lane / KC_G;
-            const int g = (lane % KC_G) ^ ((row >> KC_SWZ_SHIFT) & (KC_G - 1));
-            const int gx = x0 + row;
-            if (map.mapped()) {
-                const int src = gx < xlim ? map.row(gx) : -1;
-                L.off[q] = src >= 0 ? ((uint32_t)src * ld + g * 8) * 2u : OOB;
-            } else {
-                L.off[q] = gx < xlim ? ((uint32_t)gx * ld + g * 8) * 2u : OOB;
+#pragma unroll
+            for (int q = 0; q < (XC ? 1 : NQ); ++q) {
+                const int row = (wave + 8 * q) * 8 + (lane >> 3);
+                const int g = (lane & 7) ^ ((row >> 1) & 7);
+                const int gx = x0 + row;
+                if (map.mapped()) {
+                    const int src = gx < xlim ? map.row(gx) : -1;
+                    off[q] = src >= 0 ? ((uint32_t)src * ld + g * 8) * 2u : OOB;
+                } else {
+                    off[q] = gx < xlim ? ((uint32_t)gx * ld + g * 8) * 2u : OOB;
+                }
             }
-            L.kthr[q] = klim - g * 8;
         }
     }
-}
+    // request chunk q of the part's k-tile at origin k0 (it lands at lds + q * 8 KB); past the end of K: zeros
+    __device__ __forceinline__ void request(const i32x4 &rsrc, uint32_t lds, int k0, int ld, int q) const {
+        const int k = XC ? k0 + q * 8 * KROWS : k0;
+        const uint32_t voff = k < kthr ? off[XC ? 0 : q] : OOB;
+        load_to_lds(rsrc, lds + q * 8192, voff, XC ? (uint32_t)k * ld * 2u : (uint32_t)k * 2u);
+    }
+};
 
-// Byte offsets (inside an operand tile) from which lane `lane` reads its MFMA fragments.
-//   KC: one offset per k-step, blocks of 32 rows add 32 * KC_ROW bytes.
-//   XC: one offset per 32-column block, k-steps add 16*512 bytes, the second half 4*512.
-template <bool XC, int NBLK>
+// Byte offsets (inside an operand part) from which lane `lane` reads its MFMA fragments: lane l supplies row or
+// column l % 16 of a 16-wide block and k = 8 (l / 16) .. + 7 of a 32-deep k-step.
+//   KC: one offset per k-step, blocks of 16 rows add 16 * KC_ROW bytes.
+//   XC: one offset per 16-column block, k-steps add 32 k-rows, the second half 4 k-rows (of XC_COLS columns).
+template <bool XC, int XC_COLS>
 struct FragAddr {
-    int32_t a[XC ? NBLK : KS];
+    int32_t a[XC ? 4 : KS];
     __device__ __forceinline__ void init(int xbase, int lane) {
         if (XC) {
-            const int s = (lane >> 2) & 3;
-            const int kr = 8 * (lane >> 5) + ((lane & 15) >> 2);
-            const int glow = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+            const int kr = 8 * (lane >> 4) + ((lane & 15) >> 2);
+            const int swz = ((kr & 3) << 2) ^ ((kr >> 3 & 1) << 1);
 #pragma unroll
-            for (int b = 0; b < NBLK; ++b)
-                a[b] = kr * 512 + (((((xbase + b * 32) >> 3) ^ (s << 2)) + glow) << 4) + (lane & 1) * 8;
+            for (int b = 0; b < (XC ? 4 : 0); ++b)
+                a[b] = kr * (XC_COLS * 2) + (((((xbase + b * 16) >> 3) + ((lane & 3) >> 1)) ^ swz) << 4) + (lane & 1) * 8;
         } else {
-            // swizzle term of row = xbase + lane%32 (xbase is a multiple of 32, which the term ignores)
-            const int s = ((lane & 31) >> KC_SWZ_SHIFT) & (KC_G - 1);
+            // swizzle term of row = xbase + lane%16 (xbase is a multiple of 16, which the term ignores)
+            const int s = ((lane & 15) >> 1) & 7;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
-                a[ks] = (xbase + (lane & 31)) * KC_ROW + (((ks * 2 + (lane >> 5)) ^ s) << 4);
+                a[ks] = (xbase + (lane & 15)) * KC_ROW + (((ks * 4 + (lane >> 4)) ^ s) << 4);
         }
     }
     __device__ __forceinline__ bf16x8 read(const char *tile, int blk, int ks) const {
         if (XC) {
-            const char *p = tile + a[blk] + ks * 16 * 512;
+            const char *p = tile + a[blk] + ks * 32 * (XC_COLS * 2);
             s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
-            s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * 512));
+            s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * (XC_COLS * 2)));
             typedef __attribute__((ext_vector_type(8))) short s16x8;
             s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             return __builtin_bit_cast(bf16x8, both);
         } else {
-            return *(const bf16x8 *)(tile + a[ks] + blk * 32 * KC_ROW);
+            return *(const bf16x8 *)(tile + a[ks] + blk * 16 * KC_ROW);
         }
     }
 };
@@ -213,10 +233,9 @@ constexpr int PLAN_THREADS = 1024;
 constexpr int MAX_PLANS = 4;
 constexpr int PLAN_SLICES = 8;                 // blocks per plan: each recomputes the header and fills a slice of the tiles
 
-// Measured cost of a heavy tile by its block count, in half blocks of a full tile's main loop:
-// up to 6 blocks run through the loop that skips blocks (slower per block), 7 and 8 through the
-// full loop, 9 through the tall loop.
-__device__ __forceinline__ int tile_cost(int nblk) { return nblk >= 9 ? 19 : (nblk >= 6 ? 16 : 13); }
+// Measured cost of a heavy tile, in half blocks of a full tile's main loop: tiles of up to 8 blocks run through
+// the full loop (blocks without rows multiply zeros), 9 through the tall loop.
+__device__ __forceinline__ int tile_cost(int nblk) { return nblk >= 9 ? 19 : 16; }
 
 struct PlanDesc {
     const int32_t *kept;
@@ -376,14 +395,11 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmDesc d) {
     const uint32_t smem_addr = (uint32_t)(uintptr_t)(lds_void *)smem;
     const int tid0 = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
-    const int wm = (wave >> 2) * 128, wn = (wave & 3) * 64;
-    const int jx = wave >> 2;
-    FragAddr<AXC, 4> fa;
-    FragAddr<BXC, 2> fb;
-    fa.init(wm, tid0 & 63);
+    const int wr = wave >> 2, wn = (wave & 3) * 64;   // the wave's rows: wr * 64 .. + 63 of either 128-row half
+    FragAddr<AXC, 128> fa;
+    FragAddr<BXC, 256> fb;
+    fa.init(wr * 64, tid0 & 63);
     fb.init(wn, tid0 & 63);
-    FragAddr<BXC, 1> fbx;                        // B fragment of the wave's block in a tall tile's ninth block row
-    fbx.init(wn + jx * 32, tid0 & 63);
     int32_t *plan = (int32_t *)d.plan;
     const int4 *tiles = (const int4 *)(plan + PLAN_HDR_INTS);
     const int myx = blockIdx.x & 7;
@@ -456,37 +472,39 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmDesc d) {
     const uint32_t b_bytes = (uint32_t)(BXC ? Ke : d.N) * (uint32_t)d.ldb * 2u;
     const i32x4 A = make_rsrc(Ap, a_bytes), B = make_rsrc(Bp, b_bytes);
 
-    f32x16 acc[4][2];
+    f32x4 acc[8][4];                                 // rows: 4 blocks of the lower half, 4 of the upper one
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // Ninth 32-row block of a tall tile (rows 256..287): its 8 column blocks of 32 go one to each wave, wave
+    // (wr, wn) taking the columns wn + 32 wr .. + 31, which it holds B fragments for.
+    f32x4 accx[2][2];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    // Ninth block row of a tall tile (rows 256..287): its 8 blocks go one to each wave, wave (wm, wn)
-    // taking the column block it already holds a B fragment for: 2 (wn / 64) + wm / 128.
-    f32x16 accx;
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) accx[v] = 0.f;
+        for (int j = 0; j < 2; ++j) accx[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int nk = (Ke + BK - 1) / BK;
-    // Software pipeline.  A k-tile is 32 deep: 2 k-steps of 8 MFMAs per wave.  Tile kt lives in
-    // stage kt % NSTAGE and is requested NSTAGE-1 iterations before it is consumed, so up to
-    // (NSTAGE-1) x 32 KB are in flight per workgroup.  Each k-step has its own fragment registers
-    // (a0/b0, a1/b1), all read in the memory phase that precedes the tile's 16 MFMAs.
-    bf16x8 a0[4], b0[2], a1[4], b1[2], ax0, ax1, bx0, bx1;
-    Loader la, lb;
-    loader_init<AXC>(la, d.lda, m0, mlim, Ke, wave, lane, amap);
-    loader_init<BXC>(lb, d.ldb, n0, d.N, Ke, wave, lane);
-    // tall tile: the two 1 KB chunks of rows 256..287 are loaded by waves 0 and 5 (one wave of each
-    // ping-pong group, on different SIMDs), which therefore have 5 loads per k-tile in flight
-    const int xw = wave == 0 ? 0 : (wave == 5 ? 1 : -1);
+    // Fragments of one k-tile: all of B (kept through both MFMA phases), one half of A at a time, and one
+    // k-step of the ninth block.
+    bf16x8 af[4][KS], bf[4][KS], ax[2];
+    Loader<AXC, 2, 128> lo, hi;
+    Loader<BXC, 4, 256> lb;
+    lo.init(d.lda, m0, mlim, wave, lane, amap);
+    hi.init(d.lda, m0 + 128, mlim, wave, lane, amap);
+    lb.init(d.ldb, n0, d.N, wave, lane);
+    lo.init_k(Ke, wave, lane);
+    hi.kthr = lo.kthr;
+    lb.init_k(Ke, wave, lane);
+    // tall tile: the four 1 KB chunks of rows 256..287 are loaded by waves 0, 5, 2 and 7 (one on each SIMD,
+    // two of each ping-pong group)
+    const int xw = ((wave >> 2) ^ (wave & 1)) == 0 ? (wave & 3) : -1;
     const bool has_x = !AXC && tall && xw >= 0;
     uint32_t offx = OOB;
-    int32_t kthrx = 0;
     if (has_x) {
-        const int row = 256 + 16 * xw + (lane >> 2);
-        const int g = (lane & 3) ^ ((row >> KC_SWZ_SHIFT) & (KC_G - 1));
+        const int row = 256 + 8 * xw + (lane >> 3);
+        const int g = (lane & 7) ^ ((row >> 1) & 7);
         const int gx = m0 + row;
         if (a_index) {
             const int src = gx < mlim ? amap.row(gx) : -1;
@@ -494,149 +512,166 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmDesc d) {
         } else {
             offx = gx < mlim ? ((uint32_t)gx * d.lda + g * 8) * 2u : OOB;
         }
-        kthrx = Ke - g * 8;
     }
-    // 32-row blocks of this wave that hold valid rows (4 except in a last, partial m-tile)
-    const int rv = mlim - m0 - wm;
-    const int nvi = __builtin_amdgcn_readfirstlane(rv >= 128 ? 4 : (rv <= 0 ? 0 : (rv + 31) >> 5));
-    // Fragment reads and MFMAs of one k-step, in halves: half 0 covers a[0], a[1], b[0], b[1] and
-    // block rows 0-1, half 1 a[2], a[3] and block rows 2-3.  In a partial m-tile (full = false)
-    // blocks without valid rows are skipped.
-    auto rd_half = [&](bf16x8(&af)[4], bf16x8(&bf)[2], int stage, int ks, int half, auto full) {
-        const char *ta = smem + stage * STAGE_BYTES, *tb = ta + OPER_A_BYTES;
-        if (half == 0 && (decltype(full)::value || nvi > 0)) {
+    auto read_b = [&](int stage) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) bf[j] = fb.read(tb, j, ks);
-        }
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int i = 2 * half; i < 2 * half + 2; ++i)
-            if (decltype(full)::value || i < nvi) af[i] = fa.read(ta, i, ks);
+            for (int j = 0; j < 4; ++j) bf[j][ks] = fb.read(smem + B_AT + stage * B_BYTES, j, ks);
     };
-    auto mma_half = [&](const bf16x8(&af)[4], const bf16x8(&bf)[2], int half, auto full) {
+    auto read_a = [&](const char *half) {
 #pragma unroll
-        for (int i = 2 * half; i < 2 * half + 2; ++i)
-            if (decltype(full)::value || i < nvi) {
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) af[i][ks] = fa.read(half, i, ks);
+    };
+    // the 4 MFMAs of one block row and k-step; nothing is moved across (loads are placed between them)
+    auto mma_row = [&](int half, int ks, int i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            acc[4 * half + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j][ks], af[i][ks], acc[4 * half + i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // ninth block: k-step ks of the k-tile in stage s3
+    auto read_x = [&](int ks, int s3) {
+        const char *t = smem + A_X + s3 * X_BYTES - wr * 64 * KC_ROW;
+        ax[0] = fa.read(t, 0, ks);
+        ax[1] = fa.read(t, 1, ks);
+    };
+    auto mma_x = [&](int ks) {
+        auto cols = [&](auto first) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[j], af[i], acc[i][j], 0, 0, 0);
-            }
+                    accx[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[decltype(first)::value + j][ks], ax[i], accx[i][j], 0, 0, 0);
+        };
+        if (wr == 0) cols(std::integral_constant<int, 0>{});
+        else cols(std::integral_constant<int, 2>{});
     };
-    // one of the 2*CPW one-KB chunk loads this wave contributes to a k-tile (CPW per operand)
-    auto request_piece = [&](int kt, int stage, int piece) {
+    // one of this wave's 1 KB requests (2 for either half of A, 4 for B, per k-tile)
+    auto request_lo = [&](int kt, int s3, int q) {
+        lo.request(A, smem_addr + A_LO + s3 * HALF_BYTES + wave * 1024, kt * BK, d.lda, q);
+    };
+    auto request_hi = [&](int kt, int stage, int q) {
+        hi.request(A, smem_addr + A_HI + stage * HALF_BYTES + wave * 1024, kt * BK, d.lda, q);
+    };
+    auto request_b = [&](int kt, int stage, int q) {
+        lb.request(B, smem_addr + B_AT + stage * B_BYTES + wave * 1024, kt * BK, d.ldb, q);
+    };
+    auto request_x = [&](int kt, int s3) {            // tall tiles, waves 0, 5, 2 and 7 only
         const int k0 = kt * BK;
-        const uint32_t base = smem_addr + stage * STAGE_BYTES;
-        if (piece < CPW) {
-            const uint32_t kadd = AXC ? (uint32_t)k0 * d.lda * 2u : (uint32_t)k0 * 2u;
-            const uint32_t voff = k0 < la.kthr[piece] ? la.off[piece] + kadd : OOB;
-            load_to_lds(A, base + (uint32_t)(wave * CPW + piece) * 1024u, voff);
-        } else {
-            const int q = piece - CPW;
-            const uint32_t kadd = BXC ? (uint32_t)k0 * d.ldb * 2u : (uint32_t)k0 * 2u;
-            const uint32_t voff = k0 < lb.kthr[q] ? lb.off[q] + kadd : OOB;
-            load_to_lds(B, base + OPER_A_BYTES + (uint32_t)(wave * CPW + q) * 1024u, voff);
-        }
+        // (xw = wave % 4: the same swizzle, and so the same bound, as in the wave's other chunks)
+        load_to_lds(A, smem_addr + A_X + s3 * X_BYTES + xw * 1024, k0 < lo.kthr ? offx : OOB, (uint32_t)k0 * 2u);
     };
-    auto request_extra = [&](int kt, int stage) {     // tall tiles, waves 0 and 5 only
-        static_assert(BK == 32, "16 rows of 64 bytes per chunk");
-        const int k0 = kt * BK;
-        const uint32_t voff = k0 < kthrx ? offx + (uint32_t)k0 * 2u : OOB;
-        load_to_lds(A, smem_addr + stage * STAGE_BYTES + (uint32_t)(256 + 16 * xw) * KC_ROW, voff);
-    };
-    auto rd_extra = [&](int stage) {
-        const char *ta = smem + stage * STAGE_BYTES, *tb = ta + OPER_A_BYTES;
-        ax0 = fa.read(ta, 8 - (wm >> 5), 0);
-        ax1 = fa.read(ta, 8 - (wm >> 5), 1);
-        bx0 = fbx.read(tb, 0, 0);                 // read again rather than picked from b0 / b1: no VALU work
-        bx1 = fbx.read(tb, 0, 1);                 // between the MFMAs
-    };
-    auto mma_extra = [&](const bf16x8 &bx, const bf16x8 &ax) {
-        accx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bx, ax, accx, 0, 0, 0);
-    };
-    auto mma = [&](const bf16x8(&af)[4], const bf16x8(&bf)[2], auto full) {
-        mma_half(af, bf, 0, full);
-        mma_half(af, bf, 1, full);
-    };
-    auto request = [&](int kt, int stage) {
-#pragma unroll
-        for (int piece = 0; piece < 2 * CPW; ++piece) request_piece(kt, stage, piece);
-    };
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a1[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int j = 0; j < 2; ++j) b1[j] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    // Main loop, "ping-pong" form.  Waves w and w+4 share a SIMD.  Each wave alternates a memory
-    // phase M (request tile kt+3, read all fragments of tile kt from LDS) and a compute phase C
-    // (16 MFMAs), every phase ending in a workgroup barrier; waves 4-7 run half an iteration behind
-    // waves 0-3 (one extra barrier up front, matched by one extra barrier of waves 0-3 at the end),
-    // so on every SIMD one wave feeds the matrix pipe while the other waits on the LDS.
-    //  - tile j is complete before any wave reads it: every wave waits for its own loads of tile
-    //    kt+1 (at most the two newer tiles outstanding: 8 loads, or 10 in the two waves that load
-    //    the ninth block of a tall tile) before each barrier;
-    //  - the stage of tile kt-1 is overwritten by requests issued in M(kt), which every wave starts
-    //    only after a barrier that follows the last fragment read of tile kt-1 (lgkmcnt(0) before
-    //    the barrier that ends each M).
-    static_assert(BK == 32 && NSTAGE == 4, "the ping-pong loop is written for 32-deep tiles and 4 stages");
+    // Main loop, "ping-pong" form.  Waves w and w+4 share a SIMD.  For every k-tile each wave goes through
+    // two memory phases M and two compute phases C, every phase ending in a workgroup barrier:
+    //   M1(kt): read all of B and A's lower half of tile kt
+    //   C1(kt): 32 MFMAs, rows of the lower half;  between them, request A's upper half of tile kt+1 and its
+    //           lower half of tile kt+2
+    //   M2(kt): read A's upper half of tile kt
+    //   C2(kt): 32 MFMAs, rows of the upper half;  between them, request B of tile kt+2
+    // Waves 4-7 run one phase behind waves 0-3 (one extra barrier up front, matched by one extra barrier of
+    // waves 0-3 at the end), so on every SIMD one wave feeds the matrix pipe while the other waits on the LDS.
+    // The requests sit between the MFMAs, 4 per compute phase, because the path from L2 into LDS takes about
+    // 29 cycles per KB: in bursts at the start of the memory phases they outlasted the 512 cycles of MFMAs
+    // beside them.  With this placement and the 16 x 16 x 32 instruction, 16 experts x 1024 rows, h = f = 4096:
+    // GEMM2 442 -> 409 us (matrix pipe busy 61 -> 66 % of the cycles), dD 434 -> 398, dW 509 -> 470.
+    //  - A part is overwritten only after every wave has read it.  Upper half of tile kt+1, over tile kt-1: read
+    //    in M2(kt-1), which waves 4-7 leave (lgkmcnt(0), barrier) before waves 0-3 enter M1(kt).  Lower half of
+    //    tile kt+2, over tile kt-1 (three stages): read in M1(kt-1).  B of tile kt+2, over tile kt: read in
+    //    M1(kt), which waves 4-7 leave before waves 0-3 enter M2(kt).
+    //  - A part is complete before any wave reads it: every wave waits for its own loads at the end of each
+    //    phase, leaving outstanding the newest ones, which the two phases to come do not read.  Request order
+    //    per k-tile: C1: [ninth block of kt+2,] upper half of kt+1 (2), lower half of kt+2 (2); C2: B of kt+2 (4).
+    //      M1(kt+1) reads B of kt+1 (C2(kt-1)) and the lower half (older): at the end of C2(kt) 8 newer loads
+    //      exist, at the end of M2(kt) (the late group's place when the early one enters M1(kt+1)) 4.
+    //      M2(kt) reads the upper half of kt (C1(kt-1)): 2 + 4 newer loads at the end of M1(kt), 10 at C1(kt).
+    //  - The ninth block of a tall tile is read in both memory phases (one k-step each) and has three stages like
+    //    the lower half; the four waves that load it have one load more between the others in C1.
     const bool late_group = wave >= 4;
-    auto main_loop = [&](auto full, auto tallc) {
+    auto main_loop = [&](auto tallc) {
         constexpr bool TALLV = !AXC && decltype(tallc)::value;
-        const bool five = TALLV && has_x;   // this wave has 5 loads per k-tile in flight
-        // A wave waits until only the loads of the two newest k-tiles are outstanding.  The two waves
-        // that load the ninth block issue that fifth load in the MFMA phase (the memory phase is the
-        // longer one), so at the end of a memory phase it has not been issued yet for the newest tile.
-        auto wait_end_of_M = [&]() {                     // and lgkmcnt(0)
-            if (five) __builtin_amdgcn_s_waitcnt(0x0070 | 9);
-            else __builtin_amdgcn_s_waitcnt(0x0070 | 8);
-        };
-        auto wait_end_of_C = [&]() {
-            if (five) __builtin_amdgcn_s_waitcnt(0x0F70 | 10);
-            else __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
-        };
-        if (nk > 0) {
-#pragma unroll
-            for (int t = 0; t < NSTAGE - 1; ++t) {
-                request(t, t);
-                if (five) request_extra(t, t);
-            }
-            wait_end_of_C();                             // tile 0 has landed
-            __builtin_amdgcn_s_barrier();
-            if (late_group) __builtin_amdgcn_s_barrier();
-        }
-        int stage = 0;                                   // kt % NSTAGE
-        for (int kt = 0; kt < nk; ++kt) {
-            const int prev = stage == 0 ? NSTAGE - 1 : stage - 1;
-            // ---- M: memory phase
-            request(kt + NSTAGE - 1, prev);
-            rd_half(a0, b0, stage, 0, 0, full);
-            rd_half(a0, b0, stage, 0, 1, full);
-            rd_half(a1, b1, stage, 1, 0, full);
-            rd_half(a1, b1, stage, 1, 1, full);
-            if (TALLV) rd_extra(stage);
+        const bool five = TALLV && has_x;                // this wave issues 5 loads in C1 (the ninth block's first)
+        auto end_M = [&](auto nc, auto more) {           // at most nc loads outstanding (+ 1 with five), and lgkmcnt(0)
             __builtin_amdgcn_sched_barrier(0);
-            wait_end_of_M();
+            if (decltype(more)::value && five) __builtin_amdgcn_s_waitcnt(0x0070 | (decltype(nc)::value + 1));
+            else __builtin_amdgcn_s_waitcnt(0x0070 | decltype(nc)::value);
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            // ---- C: compute phase
             __builtin_amdgcn_s_setprio(1);
-            mma(a0, b0, full);
-            if (five) request_extra(kt + NSTAGE - 1, prev);
-            if (TALLV) mma_extra(bx0, ax0);
-            mma(a1, b1, full);
-            if (TALLV) mma_extra(bx1, ax1);
+        };
+        auto end_C = [&](auto nc) {
             __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_sched_barrier(0);
-            wait_end_of_C();
+            if (five) __builtin_amdgcn_s_waitcnt(0x0F70 | (decltype(nc)::value + 1));
+            else __builtin_amdgcn_s_waitcnt(0x0F70 | decltype(nc)::value);
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            stage = stage == NSTAGE - 1 ? 0 : stage + 1;
+        };
+        if (nk == 0) return;
+        // prologue: the requests of the k-tiles -2 and -1 in the loop's order
+        if (five) request_x(0, 0);
+        request_lo(0, 0, 0); request_lo(0, 0, 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) request_b(0, 0, q);
+        if (five) request_x(1, 1);
+        request_hi(0, 0, 0); request_hi(0, 0, 1);
+        request_lo(1, 1, 0); request_lo(1, 1, 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) request_b(1, 1, q);
+        __builtin_amdgcn_s_waitcnt(0x0F70 | 8);          // lower half and B of tile 0 (and its ninth block) have landed
+        __builtin_amdgcn_s_barrier();
+        if (late_group) __builtin_amdgcn_s_barrier();
+        int s3 = 0;                                      // kt % 3
+        auto k_tile = [&](int kt, auto stagec) {
+            constexpr int stage = decltype(stagec)::value;
+            const int s3_next2 = s3 == 0 ? 2 : s3 - 1;   // (kt + 2) % 3
+            read_b(stage);
+            read_a(smem + A_LO + s3 * HALF_BYTES);
+            if (TALLV) read_x(0, s3);
+            end_M(std::integral_constant<int, 6>{}, std::false_type{});
+            mma_row(0, 0, 0);
+            if (TALLV) {
+                if (five) request_x(kt + 2, s3_next2);
+            }
+            mma_row(0, 0, 1);
+            request_hi(kt + 1, stage ^ 1, 0);
+            mma_row(0, 0, 2); mma_row(0, 0, 3);
+            request_hi(kt + 1, stage ^ 1, 1);
+            mma_row(0, 1, 0); mma_row(0, 1, 1);
+            request_lo(kt + 2, s3_next2, 0);
+            mma_row(0, 1, 2);
+            request_lo(kt + 2, s3_next2, 1);
+            mma_row(0, 1, 3);
+            if (TALLV) mma_x(0);
+            end_C(std::integral_constant<int, 10>{});
+            read_a(smem + A_HI + stage * HALF_BYTES);
+            if (TALLV) read_x(1, s3);
+            end_M(std::integral_constant<int, 4>{}, std::true_type{});
+            mma_row(1, 0, 0); mma_row(1, 0, 1);
+            request_b(kt + 2, stage, 0);
+            mma_row(1, 0, 2); mma_row(1, 0, 3);
+            request_b(kt + 2, stage, 1);
+            mma_row(1, 1, 0); mma_row(1, 1, 1);
+            request_b(kt + 2, stage, 2);
+            mma_row(1, 1, 2);
+            request_b(kt + 2, stage, 3);
+            mma_row(1, 1, 3);
+            if (TALLV) mma_x(1);
+            end_C(std::integral_constant<int, 8>{});
+            s3 = s3 == 2 ? 0 : s3 + 1;
+        };
+        int kt = 0;
+        for (; kt + 1 < nk; kt += 2) {
+            k_tile(kt, std::integral_constant<int, 0>{});
+            k_tile(kt + 1, std::integral_constant<int, 1>{});
         }
-        if (nk > 0 && !late_group) __builtin_amdgcn_s_barrier();
+        if (kt < nk) k_tile(kt, std::integral_constant<int, 0>{});
+        if (!late_group) __builtin_amdgcn_s_barrier();
     };
-    if (tall)
-        main_loop(std::true_type{}, std::true_type{});
-    else if (nblk >= 7)        // 7 blocks: one zero block costs less than the per-block branches of the partial loop
-        main_loop(std::true_type{}, std::false_type{});
-    else
-        main_loop(std::false_type{}, std::false_type{});
+    if (tall) main_loop(std::true_type{});
+    else main_loop(std::false_type{});               // blocks without rows multiply zeros
     __builtin_amdgcn_s_waitcnt(0x0070);              // nothing may still be writing LDS when it is reused
     __syncthreads();
     int4 ent_next = make_int4(0, 0, 0, 0);
@@ -649,8 +684,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmDesc d) {
     }
 
     // Epilogue.  The MFMAs were issued with the operands swapped (B fragment first), so the
-    // accumulators hold the transposed block: lane owns output row m = lane%32 and, per group of
-    // four registers, four consecutive columns n = (v/4)*8 + (lane/32)*4 + v%4.  The tile is
+    // accumulators hold the transposed block: lane owns output row m = lane%16 and four consecutive
+    // columns n = (lane/16)*4 + v of every 16 x 16 block.  The tile is
     // converted to bf16, staged in LDS (the operand stages are free now; reads still in flight
     // from the loop's last prefetch are never used) and written out as full 512-byte rows.
     bf16_t *C = (bf16_t *)d.C + (int64_t)e * d.strideC;
@@ -658,22 +693,16 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmDesc d) {
     const int act = d.act;
     auto for_each_quad = [&](auto fn) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 8; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int vq = 0; vq < 4; ++vq) {
-                    bf16_t *pos = st + (wm + i * 32 + (lane & 31)) * CLD + wn + j * 32 + vq * 8 + (lane >> 5) * 4;
-                    f32x4 v = {acc[i][j][vq * 4], acc[i][j][vq * 4 + 1], acc[i][j][vq * 4 + 2], acc[i][j][vq * 4 + 3]};
-                    fn(pos, v);
-                }
+            for (int j = 0; j < 4; ++j)
+                fn(st + ((i >> 2) * 128 + wr * 64 + (i & 3) * 16 + (lane & 15)) * CLD + wn + j * 16 + (lane >> 4) * 4, acc[i][j]);
         if (tall) {
 #pragma unroll
-            for (int vq = 0; vq < 4; ++vq) {
-                bf16_t *pos = st + (256 + (lane & 31)) * CLD + wn + jx * 32 + vq * 8 + (lane >> 5) * 4;
-                f32x4 v = {accx[vq * 4], accx[vq * 4 + 1], accx[vq * 4 + 2], accx[vq * 4 + 3]};
-                fn(pos, v);
-            }
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    fn(st + (256 + i * 16 + (lane & 15)) * CLD + wn + wr * 32 + j * 16 + (lane >> 4) * 4, accx[i][j]);
         }
     };
     auto put4 = [](bf16_t *pos, const f32x4 &v) {
@@ -728,33 +757,28 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmDesc d) {
             if (d.C2) {
                 // Second output act'(z), which is all the backward pass needs of z.  Both values are
                 // computed in one go and staged side by side, so the tile goes out in three parts of
-                // at most 128 rows (two staging areas of 128 rows fit the LDS): the wave's block rows
-                // 0-1, its block rows 2-3, and the ninth block row of a tall tile.
+                // at most 128 rows (two staging areas of 128 rows fit the LDS): the tile's lower half,
+                // its upper half, and the ninth block row of a tall tile.
                 bf16_t *stG = st, *stH = st + 128 * CLD;
                 bf16_t *outG = (bf16_t *)d.C2 + (int64_t)e * d.strideC;
-                auto both16 = [&](const f32x16 &a, int srow, int col) __attribute__((always_inline)) {
+                auto both4 = [&](const f32x4 &a, int srow, int col) __attribute__((always_inline)) {
+                    f32x4 g, hv;
 #pragma unroll
-                    for (int vq = 0; vq < 4; ++vq) {
-                        f32x4 g, hv;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            float h1, g1;
-                            gelu_both_fast(a[vq * 4 + q], ACT, h1, g1);
-                            hv[q] = h1;
-                            g[q] = g1;
-                        }
-                        const int off = srow * CLD + col + vq * 8 + (lane >> 5) * 4;
-                        put4(stG + off, g);
-                        put4(stH + off, hv);
+                    for (int q = 0; q < 4; ++q) {
+                        float h1, g1;
+                        gelu_both_fast(a[q], ACT, h1, g1);
+                        hv[q] = h1;
+                        g[q] = g1;
                     }
+                    const int off = srow * CLD + col + (lane >> 4) * 4;
+                    put4(stG + off, g);
+                    put4(stH + off, hv);
                 };
-                // staged row sr of part `part` is tile row trow(sr)
                 auto flush_part = [&](int part, int nrows) __attribute__((always_inline)) {
                     __syncthreads();
                     for (int p = 0; p < nrows / 16; ++p) {
                         const int sr = (tid >> 5) + 16 * p;
-                        const int trow = part == 2 ? 256 + sr : (sr >> 6) * 128 + part * 64 + (sr & 63);
-                        const int gm = m0 + trow, gn = n0 + (tid & 31) * 8;
+                        const int gm = m0 + part * 128 + sr, gn = n0 + (tid & 31) * 8;
                         const u32x4 vg = *(const u32x4 *)(stG + sr * CLD + (tid & 31) * 8);
                         const u32x4 vh = *(const u32x4 *)(stH + sr * CLD + (tid & 31) * 8);
                         if (gm < mlim && gn < d.N) {
@@ -767,14 +791,17 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmDesc d) {
 #pragma unroll
                 for (int part = 0; part < 2; ++part) {
 #pragma unroll
-                    for (int ii = 0; ii < 2; ++ii)
+                    for (int i = 0; i < 4; ++i)
 #pragma unroll
-                        for (int j = 0; j < 2; ++j)
-                            both16(acc[2 * part + ii][j], (wm >> 7) * 64 + ii * 32 + (lane & 31), wn + j * 32);
+                        for (int j = 0; j < 4; ++j)
+                            both4(acc[4 * part + i][j], wr * 64 + i * 16 + (lane & 15), wn + j * 16);
                     flush_part(part, 128);
                 }
                 if (tall) {
-                    both16(accx, lane & 31, wn + jx * 32);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) both4(accx[i][j], i * 16 + (lane & 15), wn + wr * 32 + j * 16);
                     flush_part(2, 32);
                 }
             } else {
@@ -854,21 +881,10 @@ moe_status_t launch_gemm_bf16_plans(const GemmDesc *descs, int n, hipStream_t s)
     return check_launch("gemm_plan");
 }
 
-template <bool AXC, bool BXC>
-static void launch_epi(const GemmDesc &d, hipStream_t s) {
+template <bool AXC, bool BXC, int EPI>
+static void launch_one(const GemmDesc &d, hipStream_t s) {
     // persistent: one workgroup per compute unit (the LDS footprint allows no second one)
-    dim3 grid((unsigned)num_compute_units()), block(GEMM_THREADS);
-    switch (d.epi) {
-        case EPI_STORE:
-            hipLaunchKernelGGL((gemm_bf16_kernel<AXC, BXC, EPI_STORE>), grid, block, 0, s, d);
-            break;
-        case EPI_GELU:
-            hipLaunchKernelGGL((gemm_bf16_kernel<AXC, BXC, EPI_GELU>), grid, block, 0, s, d);
-            break;
-        default:
-            hipLaunchKernelGGL((gemm_bf16_kernel<AXC, BXC, EPI_DGELU>), grid, block, 0, s, d);
-            break;
-    }
+    hipLaunchKernelGGL((gemm_bf16_kernel<AXC, BXC, EPI>), dim3((unsigned)num_compute_units()), dim3(GEMM_THREADS), 0, s, d);
 }
 
 // The plan in d.plan must have been written (launch_gemm_bf16_plans) earlier on the same stream,
@@ -878,14 +894,13 @@ moe_status_t launch_gemm_bf16(const GemmDesc &d, hipStream_t s) {
         set_error("gemm_bf16: no plan");
         return MOE_ERR_INVALID_ARG;
     }
-    if (!d.a_xc && d.b_xc)
-        launch_epi<false, true>(d, s);      // forward: A [M,K], B [K,N]
-    else if (!d.a_xc && !d.b_xc)
-        launch_epi<false, false>(d, s);     // data gradient: A [M,K], B [N,K]
-    else if (d.a_xc && d.b_xc)
-        launch_epi<true, true>(d, s);       // weight gradient: A [K,M], B [K,N]
+    if (!d.a_xc && d.b_xc && d.epi == EPI_GELU) launch_one<false, true, EPI_GELU>(d, s);          // forward: A [M,K], B [K,N]
+    else if (!d.a_xc && d.b_xc && d.epi == EPI_STORE) launch_one<false, true, EPI_STORE>(d, s);
+    else if (!d.a_xc && !d.b_xc && d.epi == EPI_DGELU) launch_one<false, false, EPI_DGELU>(d, s);  // data gradient: A [M,K], B [N,K]
+    else if (!d.a_xc && !d.b_xc && d.epi == EPI_STORE) launch_one<false, false, EPI_STORE>(d, s);
+    else if (d.a_xc && d.b_xc && d.epi == EPI_STORE) launch_one<true, true, EPI_STORE>(d, s);      // weight gradient: A [K,M], B [K,N]
     else {
-        set_error("gemm_bf16: operand layout combination not built");
+        set_error("gemm_bf16: combination of operand layouts and epilogue not built");
         return MOE_ERR_UNSUPPORTED;
     }
     return check_launch("gemm_bf16");

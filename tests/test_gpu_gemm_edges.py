@@ -1,0 +1,67 @@
+"""The grouped bf16 GEMMs at the edges of their tiles, against the CPU oracle: reduction lengths around the
+64-deep k-tile (h and f for the forward and data gradients, the kept rows for the weight gradients), row counts
+around the 32-row block and the 256-row tile, output widths around 256 columns.  Tolerance: bf16 storage with fp32
+accumulation, 2e-2 per row and tile like every other parity test, plus the element bound of gpu_util."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2303_06318_amd import moe, synth
+from gpu_util import DevInputs, assert_close_everywhere, host, make_layer, tol
+
+pytestmark = pytest.mark.gpu
+
+W = synth.WORKLOADS["cfg5_6p7b_tp4_fwdbwd"]
+
+
+def route_rows(layer, rows, seed):
+    """Routing of exactly rows[e] tokens to expert e, in a shuffled order, through moe_gate on given logits."""
+    e = np.repeat(np.arange(len(rows)), rows)
+    np.random.default_rng(seed).shuffle(e)
+    logits = np.zeros((len(e), len(rows)), np.float32)
+    logits[np.arange(len(e)), e] = 1.5
+    layer.gate(None, None, logits_in=torch.from_numpy(logits).cuda())
+    return logits
+
+
+def run_rows(orc, rows, h, f, act=moe.MOE_GELU_ERF, seed=11):
+    T, E = int(sum(rows)), len(rows)
+    wl = synth.scaled(W, T=T, h=h, f=f, E=E, capacity_factor=max(rows) * E / T, seed=seed)
+    inp = synth.make_inputs(wl)
+    dev = DevInputs(inp)
+    layer = make_layer(wl, backward=True, act=act)
+    logits = route_rows(layer, rows, seed)
+    moe.moe_dispatch(layer.shape, dev.x, layer.token_of_slot, layer.buf)
+    moe.moe_expert_ffn_fwd(layer.shape, layer.buf, dev.w1, dev.w2, layer.kept, layer.z_save, layer.hact, layer.y, layer.ws)
+    moe.moe_combine(layer.shape, layer.y, layer.expert, layer.slot, layer.gate_p, layer.out)
+    layer.backward(dev.d_out, dev.x, dev.wg, dev.w1, dev.w2)
+    torch.cuda.synchronize()
+    assert host(layer.kept).tolist() == list(rows)
+    fw = orc.layer_forward(inp.x, inp.wg, inp.w1, inp.w2, wl.C, mode=act, logits=logits)
+    bw = orc.layer_backward(fw, inp.d_out, inp.x, inp.wg, inp.w1, inp.w2, mode=act)
+    t = tol(wl)
+    hact, y, d_buf = host(layer.hact), host(layer.y), host(layer.d_buf)
+    for e, k in enumerate(rows):
+        if k:
+            assert_close_everywhere("hact", hact[e, :k], fw["H"][e, :k], t)
+            assert_close_everywhere("y", y[e, :k], fw["Y"][e, :k], t)
+            assert_close_everywhere("d_buf", d_buf[e, :k], bw["dD"][e, :k], t)
+    assert_close_everywhere("d_w1", host(layer.d_w1), bw["dW1"], t)
+    assert_close_everywhere("d_w2", host(layer.d_w2), bw["dW2"], t)
+    for e, k in enumerate(rows):
+        if k == 0:
+            assert not host(layer.d_w1)[e].any() and not host(layer.d_w2)[e].any()
+
+
+@pytest.mark.parametrize("rows,h,f", [
+    ((1, 0, 33), 8, 8),                 # one short k-tile everywhere
+    ((63, 65), 56, 72),                 # just below and above one k-tile
+    ((64, 128), 64, 128),               # whole k-tiles, odd and even counts
+    ((129, 191, 0), 120, 200),          # five and six 32-row blocks
+    ((193, 256), 136, 264),             # seven and eight blocks; one column more than a tile
+    ((257, 288), 248, 256),             # nine blocks: tall tiles, the second one full
+    ((289, 576, 5), 264, 520),          # ten blocks in two tiles, eighteen in two tall ones, a handful of rows
+])
+@pytest.mark.parametrize("act", [moe.MOE_GELU_ERF, moe.MOE_GELU_TANH])
+def test_tile_edges(orc, rows, h, f, act):
+    run_rows(orc, rows, h, f, act)
