@@ -24,9 +24,9 @@ def route_rows(layer, rows, seed):
     return logits
 
 
-def run_rows(orc, rows, h, f, act=moe.MOE_GELU_ERF, seed=11):
+def run_rows(orc, rows, h, f, act=moe.MOE_GELU_ERF, seed=11, dtype="bf16"):
     T, E = int(sum(rows)), len(rows)
-    wl = synth.scaled(W, T=T, h=h, f=f, E=E, capacity_factor=max(rows) * E / T, seed=seed)
+    wl = synth.scaled(W, T=T, h=h, f=f, E=E, capacity_factor=max(rows) * E / T, seed=seed, dtype=dtype)
     inp = synth.make_inputs(wl)
     dev = DevInputs(inp)
     layer = make_layer(wl, backward=True, act=act)
@@ -65,3 +65,15 @@ def run_rows(orc, rows, h, f, act=moe.MOE_GELU_ERF, seed=11):
 @pytest.mark.parametrize("act", [moe.MOE_GELU_ERF, moe.MOE_GELU_TANH])
 def test_tile_edges(orc, rows, h, f, act):
     run_rows(orc, rows, h, f, act)
+
+
+@pytest.mark.parametrize("rows,h,f", [
+    ((1, 0, 5), 4, 4),                  # narrow tiles (32 x 32, k-tiles of 128): a few values of one tile
+    ((31, 33, 127), 124, 132),          # around the tile and the k-tile
+    ((128, 129, 2), 128, 260),          # whole k-tiles and one row more
+    ((63, 65, 0, 97) * 8, 260, 252),    # wide tiles (64 x 64, k-tiles of 32) in every GEMM
+    ((64, 96) * 16, 256, 324),
+])
+def test_tile_edges_f32(orc, rows, h, f):
+    """fp32 storage: 1e-5 per row and tile, as in the other parity tests (fp32 products and sums on both sides)."""
+    run_rows(orc, rows, h, f, dtype="f32")
