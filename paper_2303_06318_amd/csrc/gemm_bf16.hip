@@ -31,13 +31,11 @@
 //       for A, whose two 128-column halves are separate, and 512 bytes for B)
 // Rows beyond kept[e] are never read (loaded as zero) and never written.
 #include <type_traits>
-#include "moe_common.h"
+#include "gemm_bf16_parts.h"
 
 namespace moe {
 
-constexpr int BM = 256, BN = 256, BK = 64, GEMM_THREADS = 512;
-constexpr int KS = BK / 32;                    // MFMA k-steps per k-tile
-constexpr int KC_ROW = BK * 2;                 // bytes of one KC row in LDS
+constexpr int BM = 256, BN = 256;
 constexpr int LIGHT_BLOCKS = 4;                // an expert with at most this many 32-row blocks is one "light" tile
 constexpr int MAXB = 9;                        // 32-row blocks of a tile when A is a KC operand: 8, or 9 in a "tall" tile
 constexpr int A_ROWS = MAXB * 32;              // rows of the epilogue staging tile
@@ -49,169 +47,6 @@ constexpr int B_BYTES = 256 * BK * 2;          // B's k-tile (32 KB)
 constexpr int A_HI = 0, A_LO = 2 * HALF_BYTES, A_X = A_LO + 3 * HALF_BYTES, B_AT = A_X + 3 * X_BYTES;
 constexpr int CLD = BN + 8;                    // epilogue staging row (elements)
 constexpr int SMEM_BYTES = A_ROWS * CLD * 2 > B_AT + 2 * B_BYTES ? A_ROWS * CLD * 2 : B_AT + 2 * B_BYTES;
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __attribute__((address_space(3))) void lds_void;
-
-// GeLU for the bf16 epilogues: erf by the Abramowitz-Stegun 7.1.26 rational form (absolute error
-// 1.5e-7, far below bf16 resolution) with hardware exp and reciprocal; no branches.
-__device__ __forceinline__ float erf_exp_fast(float u, float &ex) {   // u >= 0; ex = exp(-u*u)
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, u, 1.0f));
-    ex = __expf(-u * u);
-    float p = fmaf(t, 1.061405429f, -1.453152027f);
-    p = fmaf(t, p, 1.421413741f);
-    p = fmaf(t, p, -0.284496736f);
-    p = fmaf(t, p, 0.254829592f);
-    return 1.0f - p * t * ex;
-}
-__device__ __forceinline__ float tanh_fast(float u) {
-    const float e2 = __expf(2.0f * u);
-    return 1.0f - 2.0f * __builtin_amdgcn_rcpf(e2 + 1.0f);
-}
-__device__ __forceinline__ float gelu_fast(float x, int act) {
-    if (act == MOE_GELU_TANH) {
-        const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-        return 0.5f * x * (1.0f + tanh_fast(u));
-    }
-    float ex;
-    const float er = erf_exp_fast(fabsf(x) * 0.7071067811865476f, ex);
-    return 0.5f * x * (1.0f + copysignf(er, x));
-}
-// GeLU and its derivative together (they share the erf / tanh and the exponential).
-__device__ __forceinline__ void gelu_both_fast(float x, int act, float &h, float &g) {
-    if (act == MOE_GELU_TANH) {
-        const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-        const float th = tanh_fast(u);
-        const float du = 0.7978845608028654f * (1.0f + 0.134145f * x * x);
-        const float phi = 0.5f * (1.0f + th);
-        h = x * phi;
-        g = phi + 0.5f * x * (1.0f - th * th) * du;
-        return;
-    }
-    float ex;
-    const float er = erf_exp_fast(fabsf(x) * 0.7071067811865476f, ex);
-    const float phi = 0.5f * (1.0f + copysignf(er, x));
-    h = x * phi;
-    g = phi + x * ex * 0.3989422804014327f;
-}
-
-// Buffer resource (raw, stride 0) over one expert's operand: lanes whose byte offset is not below
-// `bytes` -- including offsets forced to OOB -- deliver zero without a branch.
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-__device__ __forceinline__ i32x4 make_rsrc(const void *p, uint32_t bytes) {
-    const uint64_t a = (uint64_t)p;
-    i32x4 r;
-    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
-    r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
-    r[3] = 0x00020000;
-    return r;
-}
-constexpr uint32_t OOB = 0x80000000u;
-
-// One direct global -> LDS load: lane L's 16 bytes land at LDS byte address lds_addr + 16 L, taken from
-// voff (per lane) + soff (same for all lanes).
-// Written as inline assembly so that the compiler does not order later LDS reads of the *other*
-// stage behind it; completion is awaited explicitly (s_waitcnt vmcnt) before the stage is read.
-__device__ __forceinline__ void load_to_lds(const i32x4 &rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory", "m0");
-}
-
-// Where row gx of a KC operand lives in the array its resource covers, when that is not row gx itself:
-// through an index array (negative entry: no such row), or in the row shares of duplicate token dropping
-// (share gx % G, row base + gx / G of that share).
-struct RowMap {
-    const int32_t *index;
-    int32_t G, share_rows, base;          // G > 0: shares of share_rows rows each; base = first row of this expert in a share
-    __device__ __forceinline__ bool mapped() const { return index != nullptr || G > 0; }
-    __device__ __forceinline__ int row(int gx) const {
-        return index != nullptr ? index[gx] : (gx % G) * share_rows + base + gx / G;
-    }
-};
-
-// Global -> LDS copy of one operand.  A part of a tile (a half of A, the whole of B) is filled by 1 KB
-// chunks, chunk wave + 8 q by wave `wave`; lane L fills granule L of the chunk:
-//   KC chunk:   8 rows of 128 bytes,    lane L -> row L / 8,    position L % 8
-//   XC A chunk: 4 k-rows of 256 bytes,  lane L -> k-row L / 16, position L % 16
-//   XC B chunk: 2 k-rows of 512 bytes,  lane L -> k-row L / 32, position L % 32
-// Chunks of a wave are 8 apart, so the swizzle of a lane is the same in all of them, and in an XC operand
-// they differ by a whole number of k-rows, which goes into the load's scalar offset: one offset register
-// per part, whereas the rows of a KC operand are bounds-checked (or gathered) one by one.
-template <bool XC, int NQ, int XC_COLS>
-struct Loader {
-    static constexpr int KROWS = 1024 / (XC_COLS * 2);      // XC: k-rows per chunk
-    uint32_t off[XC ? 1 : NQ];           // byte offset of this lane's granule at k = 0 (OOB: outside the operand in x)
-    int32_t kthr;                        // the granule of chunk q is below klim iff k0 (XC: + q * 8 * KROWS) < kthr
-    __device__ __forceinline__ void init_k(int klim, int wave, int lane) {
-        if (XC) kthr = klim - (wave * KROWS + lane / (64 / KROWS));
-        else kthr = klim - (((lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7)) << 3);
-    }
-    __device__ __forceinline__ void init(int ld, int x0, int xlim, int wave, int lane,
-                                         const RowMap &map = RowMap{nullptr, 0, 0, 0}) {
-        if (XC) {
-            const int krow = wave * KROWS + lane / (64 / KROWS);
-            const int gx = x0 + (((lane % (64 / KROWS)) ^ ((krow & 3) << 2) ^ ((krow >> 3 & 1) << 1)) << 3);
-            off[0] = gx < xlim ? ((uint32_t)krow * ld + gx) * 2u : OOB;
-        } else {
-#pragma unroll
-            for (int q = 0; q < (XC ? 1 : NQ); ++q) {
-                const int row = (wave + 8 * q) * 8 + (lane >> 3);
-                const int g = (lane & 7) ^ ((row >> 1) & 7);
-                const int gx = x0 + row;
-                if (map.mapped()) {
-                    const int src = gx < xlim ? map.row(gx) : -1;
-                    off[q] = src >= 0 ? ((uint32_t)src * ld + g * 8) * 2u : OOB;
-                } else {
-                    off[q] = gx < xlim ? ((uint32_t)gx * ld + g * 8) * 2u : OOB;
-                }
-            }
-        }
-    }
-    // request chunk q of the part's k-tile at origin k0 (it lands at lds + q * 8 KB); past the end of K: zeros
-    __device__ __forceinline__ void request(const i32x4 &rsrc, uint32_t lds, int k0, int ld, int q) const {
-        const int k = XC ? k0 + q * 8 * KROWS : k0;
-        const uint32_t voff = k < kthr ? off[XC ? 0 : q] : OOB;
-        load_to_lds(rsrc, lds + q * 8192, voff, XC ? (uint32_t)k * ld * 2u : (uint32_t)k * 2u);
-    }
-};
-
-// Byte offsets (inside an operand part) from which lane `lane` reads its MFMA fragments: lane l supplies row or
-// column l % 16 of a 16-wide block and k = 8 (l / 16) .. + 7 of a 32-deep k-step.
-//   KC: one offset per k-step, blocks of 16 rows add 16 * KC_ROW bytes.
-//   XC: one offset per 16-column block, k-steps add 32 k-rows, the second half 4 k-rows (of XC_COLS columns).
-template <bool XC, int XC_COLS>
-struct FragAddr {
-    int32_t a[XC ? 4 : KS];
-    __device__ __forceinline__ void init(int xbase, int lane) {
-        if (XC) {
-            const int kr = 8 * (lane >> 4) + ((lane & 15) >> 2);
-            const int swz = ((kr & 3) << 2) ^ ((kr >> 3 & 1) << 1);
-#pragma unroll
-            for (int b = 0; b < (XC ? 4 : 0); ++b)
-                a[b] = kr * (XC_COLS * 2) + (((((xbase + b * 16) >> 3) + ((lane & 3) >> 1)) ^ swz) << 4) + (lane & 1) * 8;
-        } else {
-            // swizzle term of row = xbase + lane%16 (xbase is a multiple of 16, which the term ignores)
-            const int s = ((lane & 15) >> 1) & 7;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                a[ks] = (xbase + (lane & 15)) * KC_ROW + (((ks * 4 + (lane >> 4)) ^ s) << 4);
-        }
-    }
-    __device__ __forceinline__ bf16x8 read(const char *tile, int blk, int ks) const {
-        if (XC) {
-            const char *p = tile + a[blk] + ks * 32 * (XC_COLS * 2);
-            s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
-            s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * (XC_COLS * 2)));
-            typedef __attribute__((ext_vector_type(8))) short s16x8;
-            s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            return __builtin_bit_cast(bf16x8, both);
-        } else {
-            return *(const bf16x8 *)(tile + a[ks] + blk * 16 * KC_ROW);
-        }
-    }
-};
 
 // Tile plan.  An expert's rows are cut into 32-row MFMA blocks, and its nb blocks into
 // ceil(nb / maxb) m-tiles of nearly equal block counts (maxb = 9 for a KC A operand, else 8): an
@@ -865,19 +700,22 @@ moe_status_t launch_gemm_bf16_plans(const GemmDesc *descs, int n, hipStream_t s)
         return MOE_ERR_INVALID_ARG;
     }
     PlanArgs args = {};
+    int np = 0;
     for (int i = 0; i < n; ++i) {
         const GemmDesc &d = descs[i];
+        if (gemm_rows_fits(d)) continue;
         if (d.plan == nullptr || d.E > 256) {
             set_error("gemm_bf16: no plan buffer, or more than 256 experts");
             return MOE_ERR_INVALID_ARG;
         }
-        PlanDesc &p = args.p[i];
+        PlanDesc &p = args.p[np++];
         p.kept = d.kept; p.plan = (int32_t *)d.plan;
         p.E = d.E; p.M = d.M; p.K = d.K; p.nt = (d.N + BN - 1) / BN;
         p.rows_from_kept = d.rows_from_kept; p.maxb = d.a_xc ? 8 : MAXB;
         p.cus_per_xcd = num_compute_units() / 8 > 0 ? num_compute_units() / 8 : 1;
     }
-    hipLaunchKernelGGL(gemm_plan_kernel, dim3(n, PLAN_SLICES), dim3(PLAN_THREADS), 0, s, args);
+    if (np == 0) return MOE_OK;
+    hipLaunchKernelGGL(gemm_plan_kernel, dim3(np, PLAN_SLICES), dim3(PLAN_THREADS), 0, s, args);
     return check_launch("gemm_plan");
 }
 
@@ -890,6 +728,7 @@ static void launch_one(const GemmDesc &d, hipStream_t s) {
 // The plan in d.plan must have been written (launch_gemm_bf16_plans) earlier on the same stream,
 // for this descriptor's kept, E, M, N, K, rows_from_kept and A layout; a plan serves one launch.
 moe_status_t launch_gemm_bf16(const GemmDesc &d, hipStream_t s) {
+    if (gemm_rows_fits(d)) return launch_gemm_rows(d, s);
     if (d.plan == nullptr) {
         set_error("gemm_bf16: no plan");
         return MOE_ERR_INVALID_ARG;

@@ -135,9 +135,10 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(GemmDesc d) {
 
 template <int EPI, bool AXC, bool BXC>
 static void launch_f32(const GemmDesc &d, hipStream_t s) {
-    const int64_t wide = (int64_t)((d.N + 63) / 64) * ((d.M + 63) / 64) * d.E;
-    // (256: one wide tile per compute unit)
-    const bool w = wide >= 256;
+    // Wide tiles from four per compute unit on.  Forward pair of GEMMs, wide / narrow: 32 tiles 17.5 / 11.8 us,
+    // 192 tiles 37 / 26, 384 tiles 93 / 69, 640 tiles 129 / 111; with weight gradients of 2048 tiles the backward
+    // takes 144 / 155.
+    const bool w = (int64_t)((d.N + 63) / 64) * ((d.M + 63) / 64) * d.E >= 1024;
     const int t = w ? 64 : 32;
     const dim3 grid((d.N + t - 1) / t, (d.M + t - 1) / t, d.E);
     if (w) hipLaunchKernelGGL((gemm_f32_kernel<EPI, AXC, BXC, true>), grid, dim3(F32_THREADS), 0, s, d);

@@ -1,0 +1,262 @@
+// Grouped bf16 GEMM on 128-column tiles of at most 160 rows, for the forward and data-gradient GEMMs of layers whose
+// experts hold few rows or whose 256 x 256 tiles would not fill the chip.
+//
+// With few rows the weights' HBM traffic is the bound, so what counts is bytes in flight: operands go straight into
+// LDS through a ring of S k-tiles of 64 (one barrier per k-tile, requests S - 1 tiles ahead), and the workgroups
+// are not persistent, two to a compute unit where the LDS allows it, one writing its result while the other loads.
+// With at most 160 rows every weight is fetched once, by one workgroup.
+// 8 waves, 2 x 4: a wave owns 32 columns and every second 16-row block; blocks without rows are skipped.
+// Operand layouts, swizzles and the order of the sums are those of gemm_bf16.hip.
+// Both forward GEMMs, 16 experts, h = 2048, f = 8192 (weights alone at 6.4 TB/s: 168 us), against the kernel of
+// gemm_bf16.hip: 6 rows per expert 315 -> 184 us, 48 rows 286 -> 206, 100 rows 293 -> 224, 128 rows 296 -> 234.
+#include <type_traits>
+#include "gemm_bf16_parts.h"
+
+namespace moe {
+
+constexpr int RN = 128;                        // output columns per workgroup
+constexpr int RLD = RN + 8;                    // epilogue staging row (elements)
+constexpr int RB_BYTES = RN * KC_ROW;          // B's k-tile (16 KB)
+
+// DEEP = false: two workgroups per compute unit (at most 80 KB of LDS each); true: one, with a deeper ring.
+constexpr int rows_stages(int mb, bool deep) { return deep ? (mb <= 1 ? 8 : mb <= 2 ? 6 : 4) : (mb <= 1 ? 4 : mb <= 2 ? 3 : 2); }
+
+template <bool BXC, int EPI, int MB, bool DEEP>
+__global__ __launch_bounds__(GEMM_THREADS, DEEP ? 2 : 4) void gemm_rows_kernel(GemmDesc d, int nt, int mt, int total) {
+    constexpr int S = rows_stages(MB, DEEP);
+    constexpr int A_BYTES = MB * 32 * KC_ROW, STAGE = A_BYTES + RB_BYTES;
+    constexpr int QA = (4 * MB + 7) / 8;                     // 1 KB chunks of A per wave (the last one: waves 0-3 only if MB is odd)
+    static_assert(MB * 32 * RLD * 2 <= S * STAGE, "the result is staged in the operand stages");
+    __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
+    const uint32_t smem_addr = (uint32_t)(uintptr_t)(lds_void *)smem;
+    // Tiles of one expert are neighbours in the list and each XCD takes a contiguous eighth of it: they share the
+    // expert's rows in that XCD's L2.
+    const int per = (total + 7) >> 3, t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (t >= total) return;
+    const int e = t / (nt * mt), r = t - e * nt * mt, nti = r / mt, mti = r - nti * mt, n0 = nti * RN;
+    const int Me = __builtin_amdgcn_readfirstlane(d.kept[e]);
+    // the expert's 32-row blocks in m-tiles of nearly equal size
+    const int nb = (Me + 31) >> 5, mts = (nb + MB - 1) / MB;
+    if (mti >= mts) return;
+    const int bb = nb / mts, bx = nb - bb * mts;
+    const int m0 = (mti * bb + (mti < bx ? mti : bx)) * 32, mend = m0 + (bb + (mti < bx ? 1 : 0)) * 32;
+    const int mlim = Me < mend ? Me : mend;                  // rows [m0, mlim) are this tile's
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 2, wc = (wave & 3) * 32;
+    const bool has_last = MB % 2 == 0 || wave < 4;           // this wave loads QA chunks of A, otherwise QA - 1
+
+    RowMap amap = {nullptr, 0, 0, 0};
+    if (d.a_index != nullptr) amap.index = d.a_index + (int64_t)e * d.M;
+    else if (d.a_dtd_g > 1) { amap.G = d.a_dtd_g; amap.share_rows = d.E * d.a_dtd_cg; amap.base = e * d.a_dtd_cg; }
+    const bool mapped = amap.mapped();
+    const i32x4 A = make_rsrc(mapped ? (const bf16_t *)d.A : (const bf16_t *)d.A + (int64_t)e * d.strideA,
+                              (mapped ? (uint32_t)d.a_rows : (uint32_t)Me) * (uint32_t)d.lda * 2u);
+    const i32x4 B = make_rsrc((const bf16_t *)d.B + (int64_t)e * d.strideB, (uint32_t)(BXC ? d.K : d.N) * (uint32_t)d.ldb * 2u);
+
+    Loader<false, QA, 128> la;
+    Loader<BXC, 2, 128> lb;
+    la.init(d.lda, m0, mlim, wave, lane, amap);
+    lb.init(d.ldb, n0, d.N, wave, lane);
+    la.init_k(d.K, wave, lane);
+    lb.init_k(d.K, wave, lane);
+    FragAddr<false, 128> fa;
+    FragAddr<BXC, 128> fb;
+    fa.init(wr * 16, lane);
+    fb.init(wc, lane);
+
+    f32x4 acc[MB][2];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nk = (d.K + BK - 1) / BK;
+    auto request = [&](int kt, int stage) {                  // past the end of K: zeros, without memory traffic
+        const uint32_t base = smem_addr + stage * STAGE + wave * 1024;
+#pragma unroll
+        for (int q = 0; q < QA; ++q)
+            if (q < QA - 1 || has_last) la.request(A, base, kt * BK, d.lda, q);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) lb.request(B, base + A_BYTES, kt * BK, d.ldb, q);
+    };
+    // 16-row blocks 2 i + wr, i < ni, of this wave hold rows
+    const int ni = (((mlim - m0 + 15) >> 4) - wr + 1) >> 1;
+    auto main_loop = [&](auto fullc) {
+        constexpr bool FULL = decltype(fullc)::value;
+#pragma unroll
+        for (int s = 0; s < S - 1; ++s) request(s, s);
+        int stage = 0;
+        for (int kt = 0; kt < nk; ++kt) {
+            // k-tile kt has landed (S - 2 newer ones may be outstanding), and every wave has read k-tile kt - 1,
+            // whose stage the next request overwrites
+            __builtin_amdgcn_sched_barrier(0);
+            if (has_last) __builtin_amdgcn_s_waitcnt(0x0070 | ((S - 2) * (QA + 2)));
+            else __builtin_amdgcn_s_waitcnt(0x0070 | ((S - 2) * (QA + 1)));
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            request(kt + S - 1, stage == 0 ? S - 1 : stage - 1);
+            const char *ta = smem + stage * STAGE, *tb = ta + A_BYTES;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                bf16x8 bf[2];
+                if (FULL || ni > 0) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) bf[j] = fb.read(tb, j, ks);
+                }
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+                    if (FULL || i < ni) {
+                        const bf16x8 af = fa.read(ta, 2 * i, ks);
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af, acc[i][j], 0, 0, 0);
+                    }
+            }
+            stage = stage == S - 1 ? 0 : stage + 1;
+        }
+    };
+    if (ni == MB) main_loop(std::true_type{});
+    else main_loop(std::false_type{});
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0070);                      // nothing may still be writing LDS when it is reused
+    __syncthreads();
+
+    // Epilogue: lane holds output row lane % 16 and columns (lane / 16) * 4 .. + 3 of every block; staged in LDS and
+    // written out as full 256-byte row pieces.
+    bf16_t *C = (bf16_t *)d.C + (int64_t)e * d.strideC;
+    bf16_t *st = (bf16_t *)smem;
+    const int act = d.act;
+    auto for_each_quad = [&](auto fn) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+            if (i < ni) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    fn(st + ((2 * i + wr) * 16 + (lane & 15)) * RLD + wc + j * 16 + (lane >> 4) * 4, acc[i][j]);
+            }
+    };
+    auto put4 = [](bf16_t *pos, const f32x4 &v) {
+        bf16x4 o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
+        *(bf16x4 *)pos = o;
+    };
+    const int c8 = (tid & 15) * 8, gn = n0 + c8;
+    auto each_row = [&](auto fn) __attribute__((always_inline)) {
+        for (int row = tid >> 4; row < mlim - m0; row += 32)
+            if (gn < d.N) fn(m0 + row, st + row * RLD + c8);
+    };
+    auto flush = [&](bf16_t *out) __attribute__((always_inline)) {
+        __syncthreads();
+        each_row([&](int row, const bf16_t *p) { *(u32x4 *)(out + (int64_t)row * d.ldc + gn) = *(const u32x4 *)p; });
+    };
+    if (EPI == EPI_STORE) {
+        for_each_quad([&](bf16_t *pos, const f32x4 &v) { put4(pos, v); });
+        if (d.c_index == nullptr) {
+            flush(C);
+        } else {
+            // result row (if C is given) and the scaled row at its target: the staged bf16 value times the
+            // scale, rounded again -- exactly what a separate combine pass over C would produce
+            __syncthreads();
+            each_row([&](int row, const bf16_t *p) {
+                const u32x4 v = *(const u32x4 *)p;
+                const int trg = d.c_index[(int64_t)e * d.M + row];
+                const float scl = d.c_scale[(int64_t)e * d.M + row];
+                if (d.C != nullptr) *(u32x4 *)(C + (int64_t)row * d.ldc + gn) = v;
+                if (trg >= 0) {
+                    const bf16x8 b = __builtin_bit_cast(bf16x8, v);
+                    bf16x8 o;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) o[q] = (bf16_t)((float)b[q] * scl);
+                    *(u32x4 *)((bf16_t *)d.C_scatter + (int64_t)trg * d.ldc + gn) = __builtin_bit_cast(u32x4, o);
+                }
+            });
+        }
+    } else if (EPI == EPI_GELU) {
+        auto gelu_stage = [&](auto actc) __attribute__((always_inline)) {
+            constexpr int ACT = decltype(actc)::value;
+            if (d.C2) {                                      // act'(z) goes out first, act(z) waits in the accumulators
+                for_each_quad([&](bf16_t *pos, f32x4 &v) {
+                    f32x4 g;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float h1, g1;
+                        gelu_both_fast(v[q], ACT, h1, g1);
+                        v[q] = h1;
+                        g[q] = g1;
+                    }
+                    put4(pos, g);
+                });
+                flush((bf16_t *)d.C2 + (int64_t)e * d.strideC);
+                __syncthreads();
+                for_each_quad([&](bf16_t *pos, const f32x4 &v) { put4(pos, v); });
+            } else {
+                for_each_quad([&](bf16_t *pos, const f32x4 &v) {
+                    put4(pos, f32x4{gelu_fast(v[0], ACT), gelu_fast(v[1], ACT), gelu_fast(v[2], ACT), gelu_fast(v[3], ACT)});
+                });
+            }
+        };
+        if (act == MOE_GELU_TANH) gelu_stage(std::integral_constant<int, MOE_GELU_TANH>{});
+        else gelu_stage(std::integral_constant<int, MOE_GELU_ERF>{});
+        flush(C);
+    } else {
+        const bf16_t *Zin = (const bf16_t *)d.Zin + (int64_t)e * d.strideC;
+        each_row([&](int row, bf16_t *p) { *(u32x4 *)p = *(const u32x4 *)(Zin + (int64_t)row * d.ldc + gn); });
+        __syncthreads();
+        for_each_quad([&](bf16_t *pos, const f32x4 &v) {     // Zin holds act'(z)
+            const bf16x4 z = *(const bf16x4 *)pos;
+            put4(pos, f32x4{v[0] * (float)z[0], v[1] * (float)z[1], v[2] * (float)z[2], v[3] * (float)z[3]});
+        });
+        flush(C);
+    }
+}
+
+// Up to one tile per compute unit: the deep ring.  Both forward GEMMs, deep / not: 4 experts x 100 rows, h = 4096,
+// f = 8192: 136 / 177 us, 8 x 100 rows, 1024, 4096: 59 / 73; 16 x 6 rows, 2048, 8192: 184 / 194.
+constexpr int DEEP_TILES = 256;
+// Where this kernel is chosen: capacities up to ROWS_MAX rows, and beyond them as long as the 288 x 256 tiles of the
+// other kernel leave compute units without one (both measured over the two forward GEMMs, this kernel / the other):
+//   capacity 160: 16 experts, 4096, 4096 (256 tiles): 218 / 241 us;   64 experts, 2048, 2048: 241 / 274
+//   capacity 200: 16 experts, 4096, 4096: 314 / 293;                  64 experts, 2048, 2048: 333 / 293
+//   capacity 250: 8 experts, 1024, 4096 (32 and 128 tiles): 64 / 130; 4 experts, 2048, 2048 (32 tiles): 43 / 105
+//   capacity 500: 4 experts, 2048, 2048 (64 tiles): 47 / 108;         capacity 1000 (128 tiles): 66 / 133
+//   capacity 320: 4 experts, 4096, 8192 (128 and 256 tiles): 254 with this kernel for both, 231 for the first only
+constexpr int ROWS_MAX = 160;
+constexpr int ROWS_TILES = 255;
+
+template <bool BXC, int EPI, int MB>
+static void launch_rows_mb(const GemmDesc &d, hipStream_t s) {
+    const int nt = (d.N + RN - 1) / RN, mt = (d.M + MB * 32 - 1) / (MB * 32);
+    const int total = d.E * nt * mt;
+    const dim3 grid((unsigned)((total + 7) / 8 * 8)), block(GEMM_THREADS);
+    if (total <= DEEP_TILES) hipLaunchKernelGGL((gemm_rows_kernel<BXC, EPI, MB, true>), grid, block, 0, s, d, nt, mt, total);
+    else hipLaunchKernelGGL((gemm_rows_kernel<BXC, EPI, MB, false>), grid, block, 0, s, d, nt, mt, total);
+}
+
+template <bool BXC, int EPI>
+static void launch_rows(const GemmDesc &d, hipStream_t s) {
+    if (d.M <= 32) launch_rows_mb<BXC, EPI, 1>(d, s);
+    else if (d.M <= 64) launch_rows_mb<BXC, EPI, 2>(d, s);
+    else if (d.M > 128 && d.M <= 160) launch_rows_mb<BXC, EPI, 5>(d, s);
+    else launch_rows_mb<BXC, EPI, 4>(d, s);
+}
+
+bool gemm_rows_fits(const GemmDesc &d) {
+    if (!d.rows_from_kept) return false;
+    return d.M <= ROWS_MAX || (int64_t)d.E * ((d.M + 287) / 288) * ((d.N + 255) / 256) <= ROWS_TILES;
+}
+
+moe_status_t launch_gemm_rows(const GemmDesc &d, hipStream_t s) {
+    if (!gemm_rows_fits(d) || d.a_xc) {
+        set_error("gemm_rows: sizes or operand layout of another kernel");
+        return MOE_ERR_UNSUPPORTED;
+    }
+    if (d.b_xc && d.epi == EPI_GELU) launch_rows<true, EPI_GELU>(d, s);
+    else if (d.b_xc && d.epi == EPI_STORE) launch_rows<true, EPI_STORE>(d, s);
+    else if (!d.b_xc && d.epi == EPI_DGELU) launch_rows<false, EPI_DGELU>(d, s);
+    else if (!d.b_xc && d.epi == EPI_STORE) launch_rows<false, EPI_STORE>(d, s);
+    else {
+        set_error("gemm_rows: combination of operand layouts and epilogue not built");
+        return MOE_ERR_UNSUPPORTED;
+    }
+    return check_launch("gemm_rows");
+}
+
+}  // namespace moe

@@ -75,9 +75,13 @@ struct GemmDesc {
 };
 
 moe_status_t launch_gemm_f32(const GemmDesc &d, hipStream_t s);
-// bf16 path: write the tile plans of up to 4 GEMMs in one small launch, then launch each GEMM once
+// bf16 path: write the tile plans of up to 4 GEMMs in one small launch (none for those that need no plan), then
+// launch each GEMM once
 size_t gemm_bf16_plan_bytes(const GemmDesc &d);
 moe_status_t launch_gemm_bf16_plans(const GemmDesc *descs, int n, hipStream_t s);
 moe_status_t launch_gemm_bf16(const GemmDesc &d, hipStream_t s);
+// the kernel for experts with few rows (launch_gemm_bf16 chooses it by this rule; it has no plan)
+bool gemm_rows_fits(const GemmDesc &d);
+moe_status_t launch_gemm_rows(const GemmDesc &d, hipStream_t s);
 
 }  // namespace moe

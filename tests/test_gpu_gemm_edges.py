@@ -61,6 +61,10 @@ def run_rows(orc, rows, h, f, act=moe.MOE_GELU_ERF, seed=11, dtype="bf16"):
     ((193, 256), 136, 264),             # seven and eight blocks; one column more than a tile
     ((257, 288), 248, 256),             # nine blocks: tall tiles, the second one full
     ((289, 576, 5), 264, 520),          # ten blocks in two tiles, eighteen in two tall ones, a handful of rows
+    ((16, 3, 17, 32), 136, 264),        # few rows: one 32-row block, half of it empty or full
+    ((33, 64, 0, 48), 192, 128),        # two blocks; three k-tiles for a ring of three
+    ((145, 160, 160, 7), 264, 200),     # five blocks
+    ((161, 240, 225, 31), 72, 520),     # six to eight blocks
 ])
 @pytest.mark.parametrize("act", [moe.MOE_GELU_ERF, moe.MOE_GELU_TANH])
 def test_tile_edges(orc, rows, h, f, act):
