@@ -549,7 +549,12 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmDesc d) {
         auto pass = [&](int p) {
             const int row = (tid >> 5) + 16 * p, gm = m0 + row, gn = n0 + (tid & 31) * 8;
             const u32x4 v = *(const u32x4 *)(st + row * CLD + (tid & 31) * 8);
-            if (gm < mlim && gn < d.N) *(u32x4 *)(out + (int64_t)gm * d.ldc + gn) = v;
+            u32x4 *dst = (u32x4 *)(out + (int64_t)gm * d.ldc + gn);
+            if (gm < mlim && gn < d.N) {
+                // weight gradients are not read soon and would displace the operand panels from the L2
+                if (AXC) __builtin_nontemporal_store(v, dst);
+                else *dst = v;
+            }
         };
 #pragma unroll
         for (int p = 0; p < 16; ++p) pass(p);
@@ -703,7 +708,7 @@ moe_status_t launch_gemm_bf16_plans(const GemmDesc *descs, int n, hipStream_t s)
     int np = 0;
     for (int i = 0; i < n; ++i) {
         const GemmDesc &d = descs[i];
-        if (gemm_rows_fits(d)) continue;
+        if (gemm_rows_fits(d) || gemm_wgrad_fits(d)) continue;
         if (d.plan == nullptr || d.E > 256) {
             set_error("gemm_bf16: no plan buffer, or more than 256 experts");
             return MOE_ERR_INVALID_ARG;
@@ -729,6 +734,7 @@ static void launch_one(const GemmDesc &d, hipStream_t s) {
 // for this descriptor's kept, E, M, N, K, rows_from_kept and A layout; a plan serves one launch.
 moe_status_t launch_gemm_bf16(const GemmDesc &d, hipStream_t s) {
     if (gemm_rows_fits(d)) return launch_gemm_rows(d, s);
+    if (gemm_wgrad_fits(d)) return launch_gemm_wgrad(d, s);
     if (d.plan == nullptr) {
         set_error("gemm_bf16: no plan");
         return MOE_ERR_INVALID_ARG;

@@ -1,0 +1,141 @@
+// Grouped bf16 weight gradient for experts with few rows:  C[M, N] = A^T B over kept[e] rows, A [rows, M], B [rows, N].
+//
+// With a short reduction the GEMM is a stream of results: 16 experts of 2048 x 8192 write 537 MB however few rows
+// they hold.  So the result's write-out must not wait for loads, nor loads for the write-out: a workgroup walks
+// over a run of neighbouring 128 x 128 tiles of one row panel, requests run one k-tile ahead across tile ends
+// (straight into LDS, two stages), every wave writes its own 32 x 64 part through a private 2 KB of LDS as whole
+// 128-byte lines, and two workgroups share a compute unit (80 KB of LDS each; one workgroup with a ring of four
+// k-tiles was 6 % slower).  The results are stored past the caches: nothing reads them soon, and written through
+// the L2 they displace the panels (16 experts x 100 rows, 4096 x 4096, whole backward: 606 -> 535 us).
+// Weight gradient of 16 experts of 4096 x 4096 with 6 rows each: 97 us for 537 MB (a fill of them takes 80).
+// Operand layouts, swizzles and the order of the sums are those of gemm_bf16.hip.
+#include "gemm_bf16_parts.h"
+
+namespace moe {
+
+constexpr int WT = 128;                                      // tile edge
+constexpr int W_OPER = BK * WT * 2, W_STAGE = 2 * W_OPER;    // one operand's k-tile (16 KB)
+constexpr int W_OUT = 16 * 128;                              // a wave's staging area: 16 rows of 64 columns
+
+__global__ __launch_bounds__(GEMM_THREADS, 4) void gemm_wgrad_kernel(GemmDesc d, int mt, int nt, int run, int runs, int total) {
+    __shared__ __attribute__((aligned(1024))) char smem[2 * W_STAGE + 8 * W_OUT];
+    const uint32_t smem_addr = (uint32_t)(uintptr_t)(lds_void *)smem;
+    // each XCD takes a contiguous eighth of the list: the panels of one expert stay in one L2
+    const int per = (total + 7) >> 3, t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (t >= total) return;
+    const int e = t / (mt * runs), r = t - e * mt * runs, mti = r / runs, nt0 = (r - mti * runs) * run;
+    const int ntiles = nt - nt0 < run ? nt - nt0 : run;
+    const int m0 = mti * WT;
+    const int Ke = __builtin_amdgcn_readfirstlane(d.kept[e]);
+    const int nk = Ke > 0 ? (Ke + BK - 1) / BK : 1;          // no rows: one k-tile of zeros
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
+
+    const i32x4 A = make_rsrc((const bf16_t *)d.A + (int64_t)e * d.strideA, (uint32_t)Ke * (uint32_t)d.lda * 2u);
+    const i32x4 B = make_rsrc((const bf16_t *)d.B + (int64_t)e * d.strideB, (uint32_t)Ke * (uint32_t)d.ldb * 2u);
+    Loader<true, 2, WT> la, lb;
+    la.init(d.lda, m0, d.M, wave, lane);
+    lb.init(d.ldb, nt0 * WT, d.N, wave, lane);
+    la.init_k(Ke, wave, lane);
+    lb.kthr = la.kthr;
+    FragAddr<true, WT> fa, fb;
+    fa.init(wm, lane);
+    fb.init(wn, lane);
+
+    int rn = 0, rk = 0;                                      // tile of the run and k-tile of the next request
+    auto request = [&](int stage) {
+        if (rn == ntiles) return;
+        const uint32_t base = smem_addr + stage * W_STAGE + wave * 1024;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) la.request(A, base, rk * BK, d.lda, q);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) lb.request(B, base + W_OPER, rk * BK, d.ldb, q);
+        if (++rk == nk) {
+            rk = 0;
+            ++rn;
+            lb.init(d.ldb, (nt0 + rn) * WT, d.N, wave, lane);
+        }
+    };
+    f32x4 acc[2][4];
+    char *out = smem + 2 * W_STAGE + wave * W_OUT;
+    bf16_t *C = (bf16_t *)d.C + (int64_t)e * d.strideC;
+    int stage = 0;
+    request(0);
+    for (int n = 0; n < ntiles; ++n) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int kt = 0; kt < nk; ++kt) {
+            // this k-tile has landed, and every wave has read the one before it, whose stage is requested into next
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0x0070);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            request(stage ^ 1);
+            const char *ta = smem + stage * W_STAGE, *tb = ta + W_OPER;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                bf16x8 af[2], bf[4];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) af[i] = fa.read(ta, i, ks);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bf[j] = fb.read(tb, j, ks);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af[i], acc[i][j], 0, 0, 0);
+            }
+            stage ^= 1;
+        }
+        // lane holds row lane % 16 and columns (lane / 16) * 4 .. + 3 of every 16 x 16 block; 16-byte granule g of
+        // staging row r sits at position g ^ (r & 7)
+        const int n0 = (nt0 + n) * WT + wn;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int sr = lane & 15;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4 v = acc[i][j];
+                bf16x4 o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
+                *(bf16x4 *)(out + sr * 128 + (((j * 2 + (lane >> 5)) ^ (sr & 7)) << 4) + ((lane >> 4) & 1) * 8) = o;
+            }
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int row = p * 8 + (lane >> 3), gm = m0 + wm + i * 16 + row, gn = n0 + (lane & 7) * 8;
+                const u32x4 v = *(const u32x4 *)(out + row * 128 + (((lane & 7) ^ (row & 7)) << 4));
+                if (gm < d.M && gn < d.N) __builtin_nontemporal_store(v, (u32x4 *)(C + (int64_t)gm * d.ldc + gn));
+            }
+        }
+    }
+}
+
+// Where this kernel is chosen, against the kernel of gemm_bf16.hip (whole expert backward, this / the other; the
+// other one's 256 x 256 tiles in brackets):
+//   capacity up to 160:          16 experts x 100 rows, 2048 x 8192: 527 / 567 us; 64 x 48 rows, 2048 x 2048: 456 / 518;
+//                                from 200 on it loses where tiles are plenty (16 experts, 4096 x 4096 [4096]: 684 / 664 at 250)
+//   up to two tiles per unit:    8 experts, 1024 x 4096 [512]: 163 / 171 at capacity 500, 238 / 228 at 750
+//   up to one tile per unit:     4 experts, 2048 x 2048 [256]: 92 / 118 at capacity 500, 140 / 155 at 1000
+//   half of the units or fewer:  always
+bool gemm_wgrad_fits(const GemmDesc &d) {
+    if (d.rows_from_kept) return false;
+    const int64_t tiles = (int64_t)d.E * ((d.M + 255) / 256) * ((d.N + 255) / 256);
+    return d.K <= 160 || (d.K <= 512 && tiles <= 512) || (d.K <= 1024 && tiles <= 256) || tiles <= 128;
+}
+
+moe_status_t launch_gemm_wgrad(const GemmDesc &d, hipStream_t s) {
+    if (!gemm_wgrad_fits(d) || !d.a_xc || !d.b_xc || d.epi != EPI_STORE) {
+        set_error("gemm_wgrad: sizes or operand layouts of another kernel");
+        return MOE_ERR_UNSUPPORTED;
+    }
+    const int mt = (d.M + WT - 1) / WT, nt = (d.N + WT - 1) / WT;
+    // runs of up to 8 tiles, shorter ones while there would be fewer than four workgroups per compute unit
+    int run = 8;
+    while (run > 1 && (int64_t)d.E * mt * ((nt + run - 1) / run) < 1024) run >>= 1;
+    const int runs = (nt + run - 1) / run, total = d.E * mt * runs;
+    hipLaunchKernelGGL(gemm_wgrad_kernel, dim3((unsigned)((total + 7) / 8 * 8)), dim3(GEMM_THREADS), 0, s, d, mt, nt, run, runs, total);
+    return check_launch("gemm_wgrad");
+}
+
+}  // namespace moe

@@ -80,8 +80,10 @@ moe_status_t launch_gemm_f32(const GemmDesc &d, hipStream_t s);
 size_t gemm_bf16_plan_bytes(const GemmDesc &d);
 moe_status_t launch_gemm_bf16_plans(const GemmDesc *descs, int n, hipStream_t s);
 moe_status_t launch_gemm_bf16(const GemmDesc &d, hipStream_t s);
-// the kernel for experts with few rows (launch_gemm_bf16 chooses it by this rule; it has no plan)
-bool gemm_rows_fits(const GemmDesc &d);
+// kernels for experts with few rows (launch_gemm_bf16 chooses them by these rules; they have no plan)
+bool gemm_rows_fits(const GemmDesc &d);                 // forward and data-gradient GEMMs
 moe_status_t launch_gemm_rows(const GemmDesc &d, hipStream_t s);
+bool gemm_wgrad_fits(const GemmDesc &d);                // weight gradients
+moe_status_t launch_gemm_wgrad(const GemmDesc &d, hipStream_t s);
 
 }  // namespace moe

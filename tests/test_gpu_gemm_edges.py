@@ -65,6 +65,7 @@ def run_rows(orc, rows, h, f, act=moe.MOE_GELU_ERF, seed=11, dtype="bf16"):
     ((33, 64, 0, 48), 192, 128),        # two blocks; three k-tiles for a ring of three
     ((145, 160, 160, 7), 264, 200),     # five blocks
     ((161, 240, 225, 31), 72, 520),     # six to eight blocks
+    ((9, 0, 65, 20, 1, 64, 33, 2), 2056, 2064),  # weight gradient: more than one 128-column tile per workgroup
 ])
 @pytest.mark.parametrize("act", [moe.MOE_GELU_ERF, moe.MOE_GELU_TANH])
 def test_tile_edges(orc, rows, h, f, act):
