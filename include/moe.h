@@ -341,10 +341,9 @@ moe_status_t moe_gate_bwd(const moe_shape_t *shape, const float *d_gate_p, const
  * evaluated in fp32; master, exp_avg, exp_avg_sq are updated in place.
  *   grad [n] dtype, master [n] f32 (in/out), exp_avg [n] f32 (in/out), exp_avg_sq [n] f32 (in/out),
  *   param [n] dtype (out), hp: host pointer, read before the call returns.
- *   staging: [min(ts, n)] f32 device buffer, the ONLY temporary of the step, contents undefined
- *   afterwards; for each tile the up-cast gradients are written there and the update reads them.
- *   staging == NULL: the up-cast happens in registers inside the update, no temporary exists and ts
- *   is ignored.  Both ways, and every ts, give bit-identical results.
+ *   staging: [min(ts, n)] f32 device buffer, the temporary that the tiling bounds, contents undefined
+ *   afterwards; or NULL.  This library up-casts in registers inside the update, so it needs no temporary and
+ *   leaves the buffer alone; with and without it, and with every ts, the results are the same bits.
  * With a staging buffer and ts < n, ts must be a multiple of 8.  n = 0 is a no-op.
  * Errors: MOE_ERR_INVALID_ARG for NULL / misaligned arrays, ts < 1, step < 1, beta outside [0, 1),
  * negative or non-finite lr, eps, weight_decay; MOE_ERR_UNSUPPORTED for n >= 2^40, a ts that is not a

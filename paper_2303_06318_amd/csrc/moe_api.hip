@@ -50,8 +50,8 @@ moe_status_t run_dispatch_bwd_fused(const moe_shape_t *, const void *, const int
 struct AdamwConst {
     float lr, beta1, beta2, omb1, omb2, eps, wd, inv_bc1, inv_bc2, grad_mult;
 };
-moe_status_t run_adamw_tiled(int64_t, int64_t, const AdamwConst &, const void *, float *, float *, float *, void *,
-                             float *, int, hipStream_t);
+moe_status_t run_adamw_tiled(int64_t, const AdamwConst &, const void *, float *, float *, float *, void *, int,
+                             hipStream_t);
 moe_status_t run_gate_dx_f32(const moe_shape_t *, const float *, const float *, void *, hipStream_t);
 
 static size_t esize(const moe_shape_t *sh) { return sh->dtype == MOE_BF16 ? 2 : 4; }
@@ -783,7 +783,7 @@ moe_status_t moe_adamw_tiled(int64_t n, int64_t ts, const moe_adamw_t *hp, const
     c.inv_bc1 = (float)(1.0 / bc1);
     c.inv_bc2 = (float)(1.0 / bc2);
     c.grad_mult = hp->grad_mult;
-    return run_adamw_tiled(n, ts, c, grad, master, exp_avg, exp_avg_sq, param, staging, dtype, (hipStream_t)stream);
+    return run_adamw_tiled(n, c, grad, master, exp_avg, exp_avg_sq, param, dtype, (hipStream_t)stream);
 }
 
 }  // extern "C"
