@@ -28,7 +28,7 @@
  *    only enqueue work on it; there is no host synchronisation and no host read
  *    of device data (kept_e is read on the device, so launches cover C rows per
  *    expert and skip the unused part).  One exception to "only on `stream`":
- *    moe_expert_ffn_bwd (bf16) runs its two weight-gradient GEMMs on an internal
+ *    moe_expert_ffn_bwd (bf16) may run its two weight-gradient GEMMs on an internal
  *    stream that starts behind an event of `stream`, and `stream` waits for that stream's last
  *    event before the call's work is complete, so the caller still orders everything
  *    on `stream` alone.  One internal stream (and three events) exists per caller stream and device,

@@ -231,6 +231,16 @@ static SideStream *side_stream(hipStream_t caller) {
     return ss.ok ? &ss : nullptr;
 }
 
+// When the backward's GEMMs stay on the caller's stream: two streams cost about 15 us of events, and where every
+// GEMM is bound by the weights' traffic and fills the chip, running two at once only mixes reads with writes.
+// Whole expert backward, one stream / two:
+//   few rows:       16 experts x 48 rows, 4096 x 4096: 426 / 461 us; 64 x 6 rows, 2048 x 2048: 412 / 435 (100 rows: 605 / 561)
+//   small weights:  32 x 100 rows, 1024 x 1024: 70 / 79; 4 x 6 rows, 2048 x 2048: 43 / 58; 8 x 100 rows, 1024 x 4096: 90 / 91
+//                   (200 rows: 107 / 104)
+static bool bwd_one_stream(const moe_shape_t &s) {
+    return s.C <= 64 || (s.C <= 160 && (int64_t)s.E * s.h * s.f <= ((int64_t)1 << 25));
+}
+
 // Scratch of the entry point that allocates nothing (moe_expert_ffn_fwd_static): the tile plans of its two
 // GEMMs (fetch counters, share boundaries, tile queue) live in this array instead of a caller workspace.
 // Every GPU the library runs on holds its own copy at its own address until the process ends; in host
@@ -658,8 +668,8 @@ moe_status_t moe_expert_ffn_bwd(const moe_shape_t *shape, const void *d_y, const
         for (int i = 0; i < 4; ++i) { g[i].plan = pl; pl += gemm_bf16_plan_bytes(g[i]); }
         if ((st = launch_gemm_bf16_plans(g, 4, hs)) != MOE_OK) return st;
     }
-    SideStream *ss = bf ? side_stream(hs) : nullptr;
-    if (ss == nullptr) {     // fp32, or no side stream: one after the other
+    SideStream *ss = bf && !bwd_one_stream(s) ? side_stream(hs) : nullptr;
+    if (ss == nullptr) {     // one after the other
         for (int i = 0; i < 4; ++i)
             if ((st = bf ? launch_gemm_bf16(g[i], hs) : launch_gemm_f32(g[i], hs)) != MOE_OK) return st;
         return MOE_OK;
