@@ -17,50 +17,69 @@ __global__ void gate_dlogits_kernel(const float *d_gate_p, const float *probs, c
     d_logits[i] = d_gate_p[t] * pe * ((j == e ? 1.f : 0.f) - probs[i]);
 }
 
-// Block = 64 columns of x (k0..k0+63) x 4 token lanes, token chunk [t0, t1).
-//   partial[chunk][k][j] = sum_{t in chunk} x[t,k] * d_logits[t,j]
-//   d_x[t,k] += sum_j d_logits[t,j] * w_gate[k,j]
-template <typename T, int EJ>
-__global__ __launch_bounds__(256) void gate_bwd_main_kernel(const T *x, const float *w_gate, const float *d_logits,
-                                                             float *partial, T *d_x, int64_t Tn, int h, int E,
-                                                             int64_t chunk_len) {
-    __shared__ float red[4][64][EJ + 1];
-    const int c = threadIdx.x & 63, tq = threadIdx.x >> 6;
-    const int k = blockIdx.x * 64 + c;
-    const bool kin = k < h;
-    const int64_t t0 = (int64_t)blockIdx.y * chunk_len;
-    const int64_t t1 = t0 + chunk_len < Tn ? t0 + chunk_len : Tn;
-    for (int j0 = 0; j0 < E; j0 += EJ) {
-        float wg[EJ], acc[EJ];
+// d_logits and d_w_gate in one pass over x, on v_mfma_f32_16x16x4_f32 (fp32 factors as they are): for fp32 tokens,
+// and for bf16 tokens while there are few of them.  A workgroup of 16 waves owns 64 columns of x and one token
+// chunk; it makes the d_logits of 256 tokens at a time in LDS (the workgroups of the first column block also write
+// them out), every wave multiplies 16 of these tokens, and the 16 partial [64 x 16 experts] results are summed
+// through LDS in wave order.  More than 16 experts: one pass over x per 16 of them.
+//   out[chunk][k][j] = sum_{t in chunk} x[t,k] * d_logits[t,j]      (one chunk: out is d_w_gate itself)
+// Lane l supplies x columns c0 + 4 (l % 16) + c of token 4 s + l / 16, and expert l % 16 of the same token.
+// fp32, 2048 tokens, h = 1024, E = 8: 95 us as three kernels on vector FMAs, now 14.6 (with d_x: 40 -> 8.7).
+template <typename XT>
+__global__ __launch_bounds__(1024) void gate_dwg_direct_kernel(const float *d_gate_p, const float *probs, const int32_t *expert,
+                                                               const XT *x, float *d_logits, float *out, int64_t T, int h,
+                                                               int E, int64_t chunk_len) {
+    constexpr int TOK = 256;
+    __shared__ float dl[TOK][17];
+    __shared__ float red[16][64][17];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n16 = lane & 15, g = lane >> 4;
+    const int c0 = blockIdx.x * 64, col = c0 + 4 * n16;
+    const int64_t t0 = (int64_t)blockIdx.y * chunk_len, t1 = t0 + chunk_len < T ? t0 + chunk_len : T;
+    for (int j0 = 0; j0 < E; j0 += 16) {
+        f32x4 acc[4];
 #pragma unroll
-        for (int j = 0; j < EJ; ++j) {
-            wg[j] = (kin && j0 + j < E) ? w_gate[(int64_t)k * E + j0 + j] : 0.f;
-            acc[j] = 0.f;
-        }
-        for (int64_t t = t0 + tq; t < t1; t += 4) {
-            const float *dl = d_logits + t * E + j0;
-            const float xv = kin ? (float)x[t * h + k] : 0.f;
-            float dxa = 0.f;
+        for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int64_t tb = t0; tb < t1; tb += TOK) {
+            f32x4 xv[4];
 #pragma unroll
-            for (int j = 0; j < EJ; ++j) {
-                const float g = (j0 + j < E) ? dl[j] : 0.f;
-                acc[j] = fmaf(xv, g, acc[j]);
-                dxa = fmaf(g, wg[j], dxa);
+            for (int s = 0; s < 4; ++s) {                        // clamped addresses, zeros selected afterwards
+                const int64_t t = tb + wave * 16 + 4 * s + g;
+                const bool in = (t < t1) & (col < h);
+                xv[s] = load4(x + (in ? t * h + col : 0));
+                if (!in) xv[s] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
-            if (d_x && kin) d_x[t * h + k] = (T)((float)d_x[t * h + k] + dxa);
-        }
+            __syncthreads();                                     // the previous tokens' d_logits have been read
 #pragma unroll
-        for (int j = 0; j < EJ; ++j) red[tq][c][j] = acc[j];
+            for (int q = 0; q < 4; ++q) {
+                const int tt = (tid >> 4) + 64 * q, e = j0 + (tid & 15);
+                const int64_t t = tb + tt;
+                float v = 0.f;
+                if (t < t1 && e < E) {
+                    const int et = expert[t];
+                    v = d_gate_p[t] * probs[t * E + et] * ((e == et ? 1.f : 0.f) - probs[t * E + e]);
+                    if (blockIdx.x == 0) d_logits[t * E + e] = v;
+                }
+                dl[tt][tid & 15] = v;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const float b = dl[wave * 16 + 4 * s + g][n16];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[s][c], b, acc[c], 0, 0, 0);
+            }
+        }
+        // lane holds expert n16 and, of acc[c], rows r = 4 g + v <-> columns 4 r + c
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave][4 * (4 * g + v) + c][n16] = acc[c][v];
         __syncthreads();
-        if (partial) {
-            for (int i = threadIdx.x; i < 64 * EJ; i += 256) {
-                int cc = i / EJ, j = i - cc * EJ;
-                int kk = blockIdx.x * 64 + cc;
-                if (kk < h && j0 + j < E)
-                    partial[((int64_t)blockIdx.y * h + kk) * E + j0 + j] =
-                        (red[0][cc][j] + red[1][cc][j]) + (red[2][cc][j] + red[3][cc][j]);
-            }
-        }
+        const int cc = tid >> 4, e = j0 + (tid & 15);
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) sum += red[w][cc][tid & 15];
+        if (c0 + cc < h && e < E) out[((int64_t)blockIdx.y * h + c0 + cc) * E + e] = sum;
         __syncthreads();
     }
 }
@@ -541,51 +560,90 @@ __global__ __launch_bounds__(256, KS == 1 ? 2 : 1) void gate_dx_rows_kernel(
     }
 }
 
+// The same result, d_x[t,:] = d_buf row (or d_x itself) + d_logits[t,:] w_gate^T, on v_mfma_f32_16x16x4_f32 for fp32
+// tokens, and for bf16 tokens while there are few of them: a workgroup takes 64 tokens x 64 columns (the kernel above
+// 192 x 512: a short token tensor gives it less than a workgroup per compute unit), a wave 16 tokens, without LDS.
+// Lane l supplies token l % 16 and expert 4 s + l / 16, and Wg column c0 + 4 (l % 16) + b of that expert for result
+// block b, so that it ends up with four consecutive columns of the tokens 4 (l / 16) + v.
+template <typename XT, bool GATHER>
+__global__ __launch_bounds__(256) void gate_dx_direct_kernel(const float *w_gate, const float *d_logits, XT *d_x, int64_t T,
+                                                             int h, int E, const XT *d_buf, const int32_t *expert,
+                                                             const int32_t *slot, int64_t Cg, int G, int col_blocks) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n16 = lane & 15, g = lane >> 4;
+    const int64_t tblk = blockIdx.x / (unsigned)col_blocks;
+    const int c0 = (int)(blockIdx.x - tblk * col_blocks) * 64, col = c0 + 4 * n16;
+    const int64_t t0 = tblk * 64 + wave * 16;
+    const bool cin = col < h;
+    f32x4 rows[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {                                // loads from clamped addresses, zeros selected afterwards
+        const int64_t t = t0 + 4 * g + v, tc = t < T ? t : 0;
+        const XT *src = d_x + tc * h;
+        bool in = cin;
+        if (GATHER) {
+            const int sl = slot[tc];
+            in = in & (sl >= 0);
+            src = d_buf + (in ? (((int64_t)(sl % G) * E + expert[tc]) * Cg + sl / G) * h : 0);
+        }
+        rows[v] = load4(src + (in ? col : 0));
+        if (!in) rows[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    f32x4 acc[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int64_t ta = t0 + n16 < T ? t0 + n16 : 0;
+    for (int e0 = 0; e0 < E; e0 += 16) {
+        float a[4], w[4][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int e = e0 + 4 * s + g;
+            const bool in = e < E;
+            const float av = d_logits[ta * E + (in ? e : 0)];
+            a[s] = in ? av : 0.f;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const float wv = w_gate[(int64_t)(cin ? col + b : 0) * E + (in ? e : 0)];
+                w[s][b] = in ? wv : 0.f;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], w[s][b], acc[b], 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int64_t t = t0 + 4 * g + v;
+        if (cin && t < T) store4(d_x + t * h + col, f32x4{rows[v][0] + acc[0][v], rows[v][1] + acc[1][v], rows[v][2] + acc[2][v], rows[v][3] + acc[3][v]});
+    }
+}
+
 // ------------------------------------------------------------------ host side
-static int simple_chunks(const moe_shape_t *sh) {
+static int direct_chunks(const moe_shape_t *sh) {
     int64_t n = (sh->T + 1023) / 1024;
     return (int)(n < 1 ? 1 : (n > 32 ? 32 : n));
 }
 
 
-template <typename T>
-static void launch_gate_bwd_main(const moe_shape_t *sh, const void *x, const float *w_gate, const float *d_logits,
-                                 float *partial, void *d_x, int nch, int64_t chunk_len, hipStream_t s) {
-    dim3 grid((sh->h + 63) / 64, nch), block(256);
-    if (sh->E <= 16)
-        hipLaunchKernelGGL((gate_bwd_main_kernel<T, 16>), grid, block, 0, s, (const T *)x, w_gate, d_logits, partial,
-                           (T *)d_x, sh->T, sh->h, sh->E, chunk_len);
-    else if (sh->E <= 32)
-        hipLaunchKernelGGL((gate_bwd_main_kernel<T, 32>), grid, block, 0, s, (const T *)x, w_gate, d_logits, partial,
-                           (T *)d_x, sh->T, sh->h, sh->E, chunk_len);
+// d_logits and d_w_gate (not null) by the one-pass kernel; `partial` holds direct_chunks * h * E floats and is unused
+// for one chunk (bf16 tokens take this way only with one)
+static void launch_dwg_direct(const moe_shape_t *sh, const float *d_gate_p, const float *probs, const int32_t *expert,
+                              const void *x, float *d_logits, float *d_w_gate, float *partial, hipStream_t s) {
+    const int nch = direct_chunks(sh);
+    const int64_t chunk_len = (sh->T + nch - 1) / nch;
+    const dim3 grid((unsigned)((sh->h + 63) / 64), (unsigned)nch), block(1024);
+    float *out = nch > 1 ? partial : d_w_gate;
+    if (sh->dtype == MOE_F32)
+        hipLaunchKernelGGL((gate_dwg_direct_kernel<float>), grid, block, 0, s, d_gate_p, probs, expert, (const float *)x,
+                           d_logits, out, sh->T, sh->h, sh->E, chunk_len);
     else
-        hipLaunchKernelGGL((gate_bwd_main_kernel<T, 64>), grid, block, 0, s, (const T *)x, w_gate, d_logits, partial,
-                           (T *)d_x, sh->T, sh->h, sh->E, chunk_len);
-}
-
-static moe_status_t run_gate_bwd_simple(const moe_shape_t *sh, const float *d_gate_p, const float *probs, const int32_t *expert,
-                          const void *x, const float *w_gate, float *d_logits, float *d_w_gate, void *d_x_accum,
-                          void *ws, hipStream_t s) {
-    const int64_t n = sh->T * sh->E;
-    hipLaunchKernelGGL(gate_dlogits_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d_gate_p, probs,
-                       expert, d_logits, sh->T, sh->E);
-    if (d_w_gate || d_x_accum) {
-        const int nch = simple_chunks(sh);
-        const int64_t chunk_len = (sh->T + nch - 1) / nch;
-        float *partial = d_w_gate ? (float *)ws : nullptr;
-        if (sh->dtype == MOE_BF16)
-            launch_gate_bwd_main<bf16_t>(sh, x, w_gate, d_logits, partial, d_x_accum, nch, chunk_len, s);
-        else
-            launch_gate_bwd_main<float>(sh, x, w_gate, d_logits, partial, d_x_accum, nch, chunk_len, s);
-        if (d_w_gate) {
-            const int64_t m = (int64_t)sh->h * sh->E;
-            hipLaunchKernelGGL(gate_dwg_reduce_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, partial,
-                               d_w_gate, m, nch);
-        }
+        hipLaunchKernelGGL((gate_dwg_direct_kernel<bf16_t>), grid, block, 0, s, d_gate_p, probs, expert, (const bf16_t *)x,
+                           d_logits, out, sh->T, sh->h, sh->E, chunk_len);
+    if (nch > 1) {
+        const int64_t m = (int64_t)sh->h * sh->E;
+        hipLaunchKernelGGL(gate_dwg_reduce_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, partial, d_w_gate, m, nch);
     }
-    return check_launch("gate_bwd");
 }
-
 
 // ---- workspace layout of the bf16 path: [planes 3*Epad*Tpad bf16][partial nchunks*Epad*h fp32]
 static int epad_of(int E) { return (E + 15) / 16 * 16; }
@@ -606,7 +664,7 @@ static size_t planes_bytes(const moe_shape_t *sh) {
 size_t gate_bwd_ws_bytes(const moe_shape_t *sh) {
     if (sh->dtype == MOE_BF16)
         return planes_bytes(sh) + (size_t)dwg_chunks(sh) * epad_of(sh->E) * sh->h * 4;
-    return (size_t)simple_chunks(sh) * sh->h * sh->E * 4;
+    return (size_t)direct_chunks(sh) * sh->h * sh->E * 4;
 }
 
 template <int CW, int EJ>
@@ -659,17 +717,45 @@ static void launch_dx_mfma(const moe_shape_t *sh, const float *w_gate, const flo
 #undef MOE_DX_ROWS
 }
 
+template <typename XT>
+static void launch_dx_direct_as(const moe_shape_t *sh, const float *w_gate, const float *d_logits, void *d_x, hipStream_t s,
+                                const void *d_buf, const int32_t *expert, const int32_t *slot, int tp_size) {
+    const int col_blocks = (sh->h + 63) / 64;
+    const dim3 grid((unsigned)((sh->T + 63) / 64 * col_blocks)), block(256);
+    const int64_t Cg = (sh->C + tp_size - 1) / tp_size;
+    if (d_buf) hipLaunchKernelGGL((gate_dx_direct_kernel<XT, true>), grid, block, 0, s, w_gate, d_logits, (XT *)d_x, sh->T, sh->h,
+                                  sh->E, (const XT *)d_buf, expert, slot, Cg, tp_size, col_blocks);
+    else hipLaunchKernelGGL((gate_dx_direct_kernel<XT, false>), grid, block, 0, s, w_gate, d_logits, (XT *)d_x, sh->T, sh->h, sh->E,
+                            (const XT *)nullptr, expert, slot, Cg, tp_size, col_blocks);
+}
+static void launch_dx_direct(const moe_shape_t *sh, const float *w_gate, const float *d_logits, void *d_x, hipStream_t s,
+                             const void *d_buf = nullptr, const int32_t *expert = nullptr, const int32_t *slot = nullptr,
+                             int tp_size = 1) {
+    if (sh->dtype == MOE_F32) launch_dx_direct_as<float>(sh, w_gate, d_logits, d_x, s, d_buf, expert, slot, tp_size);
+    else launch_dx_direct_as<bf16_t>(sh, w_gate, d_logits, d_x, s, d_buf, expert, slot, tp_size);
+}
+
+// Where the fp32-instruction kernels serve bf16 tokens, against the bf16 matrix-core kernels (us, these / those):
+//   d_w_gate:  h = 2048, E = 16: 256 tokens 8.4 / 14.5, 1024 tokens 13.4 / 14.6, 2048 tokens 15.8 / 14.4;
+//              E = 64 (a pass over x per 16 experts): 100 tokens 14.5 / 15.3, 256 tokens 16.6 / 15.4
+//   d_x:       E = 16: h = 2048: 1024 tokens 8.2 / 15.5, 2048 tokens 13.4 / 15.9, 4096 tokens 28 / 18.5; h = 4096: 1024 tokens
+//              13.6 / 16.0, 2048 tokens 28 / 18.8;  h = 2048, E = 64: 1024 tokens 21.5 / 31.8, 2048 tokens 40 / 32
+static bool dwg_direct(const moe_shape_t *sh) { return sh->dtype == MOE_F32 || sh->T <= (sh->E <= 16 ? 1024 : 128); }
+static bool dx_direct(const moe_shape_t *sh) {
+    return sh->dtype == MOE_F32 || sh->T * sh->h <= (int64_t)1 << (sh->E <= 32 ? 22 : 21);
+}
+
 moe_status_t run_gate_bwd(const moe_shape_t *sh, const float *d_gate_p, const float *probs, const int32_t *expert,
                           const void *x, const float *w_gate, float *d_logits, float *d_w_gate, void *d_x_accum,
                           void *ws, hipStream_t s) {
-    if (sh->dtype != MOE_BF16)
-        return run_gate_bwd_simple(sh, d_gate_p, probs, expert, x, w_gate, d_logits, d_w_gate, d_x_accum, ws, s);
     const int E = sh->E, Epad = epad_of(E);
     const int64_t T = sh->T, Tpad = tpad_of(T);
     if (!d_w_gate) {
         const int64_t n = T * E;
         hipLaunchKernelGGL(gate_dlogits_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d_gate_p, probs,
                            expert, d_logits, T, E);
+    } else if (dwg_direct(sh)) {
+        launch_dwg_direct(sh, d_gate_p, probs, expert, x, d_logits, d_w_gate, (float *)ws, s);
     } else {
         bf16_t *planes = (bf16_t *)ws;
         float *partial = (float *)((char *)ws + planes_bytes(sh));
@@ -698,39 +784,22 @@ moe_status_t run_gate_bwd(const moe_shape_t *sh, const float *d_gate_p, const fl
                            d_w_gate, sh->h, E, Epad, nch);
     }
     if (d_x_accum) {
-        if (dx_rows_ok(sh)) launch_dx_mfma(sh, w_gate, d_logits, d_x_accum, s);
+        if (dx_direct(sh)) launch_dx_direct(sh, w_gate, d_logits, d_x_accum, s);
+        else if (dx_rows_ok(sh)) launch_dx_mfma(sh, w_gate, d_logits, d_x_accum, s);
         else
             for (int j0 = 0; j0 < E; j0 += 64) launch_dx<2, 64>(sh, w_gate, d_logits, d_x_accum, j0, s);
     }
     return check_launch("gate_bwd");
 }
 
-// fp32 storage: d_x[t,k] += sum_j d_logits[t,j] * w_gate[k,j], one thread per element (small workloads only)
-__global__ void gate_dx_f32_kernel(const float *w_gate, const float *d_logits, float *d_x, int64_t T, int h, int E) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= T * h) return;
-    const int64_t t = i / h;
-    const int k = (int)(i - t * h);
-    float s = 0.f;
-    for (int j = 0; j < E; ++j) s = fmaf(d_logits[t * E + j], w_gate[(int64_t)k * E + j], s);
-    d_x[i] += s;
-}
-
-moe_status_t run_gate_dx_f32(const moe_shape_t *sh, const float *d_logits, const float *w_gate, void *d_x,
-                             hipStream_t s) {
-    const int64_t n = sh->T * sh->h;
-    hipLaunchKernelGGL(gate_dx_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w_gate, d_logits,
-                       (float *)d_x, sh->T, sh->h, sh->E);
-    return check_launch("gate_dx_f32");
-}
-
-// Dispatch backward with the gate's contribution fused in (bf16 storage):
+// Dispatch backward with the gate's contribution fused in:
 //   d_x[t,:] = d_buf[expert[t], slot[t], :] (or 0) + d_logits[t,:] w_gate^T
 moe_status_t run_dispatch_bwd_fused(const moe_shape_t *sh, const void *d_buf, const int32_t *expert,
                                     const int32_t *slot, void *d_x, const float *d_logits, const float *w_gate,
                                     hipStream_t s, int tp_size) {
     const int E = sh->E;
-    if (dx_rows_ok(sh, tp_size)) launch_dx_mfma(sh, w_gate, d_logits, d_x, s, d_buf, expert, slot, tp_size);
+    if (dx_direct(sh)) launch_dx_direct(sh, w_gate, d_logits, d_x, s, d_buf, expert, slot, tp_size);
+    else if (dx_rows_ok(sh, tp_size)) launch_dx_mfma(sh, w_gate, d_logits, d_x, s, d_buf, expert, slot, tp_size);
     else {
         launch_dx<2, 64>(sh, w_gate, d_logits, d_x, 0, s, d_buf, expert, slot, tp_size);
         for (int j0 = 64; j0 < E; j0 += 64) launch_dx<2, 64>(sh, w_gate, d_logits, d_x, j0, s);

@@ -4,11 +4,11 @@
 // by splitting every weight into three bf16 pieces (hi + mid + lo == w to ~2^-24) and issuing
 // three bf16 MFMAs into one fp32 accumulator; bf16 x bf16 products are exact in fp32, so the
 // result has fp32 dot-product accuracy while X is streamed once at HBM speed.
-// fp32 tokens: plain fp32 FMA dot products (small workloads only).
+// fp32 tokens, and short bf16 token tensors: fp32 matrix instructions on the operands as they are.
 //
 // Routing: per-token-block histograms of the chosen experts (integer LDS atomics: the result does not
-// depend on their order), written by the gate kernel itself for bf16 tokens (a block = the 64 or 16
-// tokens of a workgroup) and by a small kernel otherwise (blocks of 1024 tokens); then one kernel in
+// depend on their order), written by the gate kernel itself (a block = the 64 or 16 tokens of a
+// workgroup) and by a small kernel when the logits are given (blocks of 1024 tokens); then one kernel in
 // which every block of 1024 tokens adds up the histograms of the tokens before it (all threads in
 // parallel, integer atomics again), ranks its own tokens with wave ballots (token order inside a wave
 // = lane order) and writes slot / token_of_slot; the last block writes counts and kept.
@@ -32,6 +32,57 @@ __global__ void gate_split_wg_kernel(const float *wg, bf16_t *planes, int h, int
     planes[i] = hi;
     planes[n + i] = mid;
     planes[2 * n + i] = lo;
+}
+
+// ------------------------------------------------------------------ choice of the expert, from the logits in LDS
+// (all threads of the workgroup of TM tokens; the logits are complete before the call)
+template <int EP, int TM, int THREADS>
+__device__ __forceinline__ void gate_choose(const float (*lg)[EP + 1], int32_t *hist_s, float *probs, int32_t *expert,
+                                            float *gate_p, int64_t T, int E, int32_t *hist, int32_t *token_of_slot,
+                                            int64_t EC) {
+    const int tid = threadIdx.x;
+    const int64_t t0 = (int64_t)blockIdx.x * TM;
+    if (tid < EP) hist_s[tid] = 0;
+    __syncthreads();
+    // Softmax and top-1 with TPT adjacent lanes per token: lane `sub` looks at experts sub, sub + TPT, ...;
+    // the lanes' candidates are merged by butterfly exchanges (larger logit wins, the lower index among
+    // equal ones: the same choice as a left-to-right scan with a strict comparison).
+    constexpr int TPT = THREADS / TM;
+    static_assert(TPT >= 1 && (TPT & (TPT - 1)) == 0 && TPT <= 64, "lanes per token");
+    const int tt = tid / TPT, sub = tid % TPT;
+    const float *row = &lg[tt][0];
+    float best = -__builtin_inff();
+    int bi = 0x7fffffff;
+    for (int j = sub; j < E; j += TPT) {
+        const float v = row[j];
+        if (v > best || bi == 0x7fffffff) { best = v; bi = j; }      // strict: the first of equal values stays
+    }
+#pragma unroll
+    for (int o = 1; o < TPT; o <<= 1) {
+        const float ov = __shfl_xor(best, o);
+        const int oi = __shfl_xor(bi, o);
+        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+    }
+    float denom = 0.f;
+    for (int j = sub; j < E; j += TPT) denom += expf(row[j] - best);
+#pragma unroll
+    for (int o = 1; o < TPT; o <<= 1) denom += __shfl_xor(denom, o);
+    const float inv = 1.0f / denom;
+    const int64_t t = t0 + tt;
+    if (t < T) {
+        if (probs)
+            for (int j = sub; j < E; j += TPT) probs[t * E + j] = expf(row[j] - best) * inv;
+        if (sub == 0) {
+            expert[t] = bi;
+            gate_p[t] = inv;
+            atomicAdd(&hist_s[bi], 1);
+        }
+    }
+    __syncthreads();
+    // the routing kernel's inputs: this block's histogram, and its share of the inverse map cleared
+    if (tid < E) hist[(int64_t)blockIdx.x * E + tid] = hist_s[tid];
+    const int64_t per = (EC + gridDim.x - 1) / gridDim.x, i0 = (int64_t)blockIdx.x * per;
+    for (int64_t i = i0 + tid; i < i0 + per && i < EC; i += THREADS) token_of_slot[i] = -1;
 }
 
 // ------------------------------------------------------------------ fused gate, bf16 tokens
@@ -153,72 +204,73 @@ __global__ __launch_bounds__(64 * NW) void gate_bf16_kernel(const bf16_t *x, con
         part[0][tt][j] = v;
         if (t0 + tt < T) logits[(t0 + tt) * E + j] = v;
     }
-    if (tid < EP) hist_s[tid] = 0;
-    __syncthreads();
-    // Softmax and top-1 with TPT adjacent lanes per token: lane `sub` looks at experts sub, sub + TPT, ...;
-    // the lanes' candidates are merged by butterfly exchanges (larger logit wins, the lower index among
-    // equal ones: the same choice as a left-to-right scan with a strict comparison).
-    constexpr int TPT = 64 * NW / TM;
-    static_assert(TPT >= 1 && (TPT & (TPT - 1)) == 0 && TPT <= 64, "lanes per token");
-    const int tt = tid / TPT, sub = tid % TPT;
-    const float *row = &part[0][tt][0];
-    float best = -__builtin_inff();
-    int bi = 0x7fffffff;
-    for (int j = sub; j < E; j += TPT) {
-        const float v = row[j];
-        if (v > best || bi == 0x7fffffff) { best = v; bi = j; }      // strict: the first of equal values stays
-    }
-#pragma unroll
-    for (int o = 1; o < TPT; o <<= 1) {
-        const float ov = __shfl_xor(best, o);
-        const int oi = __shfl_xor(bi, o);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-    }
-    float denom = 0.f;
-    for (int j = sub; j < E; j += TPT) denom += expf(row[j] - best);
-#pragma unroll
-    for (int o = 1; o < TPT; o <<= 1) denom += __shfl_xor(denom, o);
-    const float inv = 1.0f / denom;
-    const int64_t t = t0 + tt;
-    if (t < T) {
-        if (probs)
-            for (int j = sub; j < E; j += TPT) probs[t * E + j] = expf(row[j] - best) * inv;
-        if (sub == 0) {
-            expert[t] = bi;
-            gate_p[t] = inv;
-            atomicAdd(&hist_s[bi], 1);
-        }
-    }
-    __syncthreads();
-    // the routing kernel's inputs: this block's histogram, and its share of the inverse map cleared
-    if (tid < E) hist[(int64_t)blockIdx.x * E + tid] = hist_s[tid];
-    const int64_t per = (EC + gridDim.x - 1) / gridDim.x, i0 = (int64_t)blockIdx.x * per;
-    for (int64_t i = i0 + tid; i < i0 + per && i < EC; i += 64 * NW) token_of_slot[i] = -1;
+    gate_choose<EP, TM, 64 * NW>(part[0], hist_s, probs, expert, gate_p, T, E, hist, token_of_slot, EC);
 }
 
-// ------------------------------------------------------------------ fp32 tokens: logits by fp32 FMA, one wave per token
-__global__ __launch_bounds__(256) void gate_logits_f32_kernel(const float *x, const float *wg, const float *bias,
-                                                              float *logits, int64_t T, int h, int E) {
-    const int lane = threadIdx.x & 63;
-    const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= T) return;
-    for (int j0 = 0; j0 < E; j0 += 16) {
-        float acc[16];
+// ------------------------------------------------------------------ fp32 matrix instruction
+// The whole gate of 16 tokens per workgroup on v_mfma_f32_16x16x4_f32, for fp32 tokens, and for bf16 tokens while
+// there are few of them: Wg is used as it is stored, without planes and the launch that makes them, and 16 tokens
+// per workgroup spread a short token tensor over four times as many compute units as 64 do.
+// The 8 waves split the reduction (16 k per step, U steps in flight); lane l supplies token l % 16 and expert l % 16
+// with k = 4 (l / 16) + j to the j-th of four instructions.  A launch-latency kernel: fp32, 2048 tokens, h = 1024, E = 8:
+// 42 us for the whole moe_gate call with vector FMAs, a softmax kernel and a histogram kernel, now 11.7.
+template <typename XT, int NT, int U>
+__global__ __launch_bounds__(512) void gate_direct_kernel(const XT *x, const float *wg, const float *bias, float *logits,
+                                                          float *probs, int32_t *expert, float *gate_p, int64_t T, int h,
+                                                          int E, int32_t *hist, int32_t *token_of_slot, int64_t EC) {
+    constexpr int EP = NT * 16, TM = 16, NW = 8;
+    __shared__ float part[NW][TM][EP + 1];
+    __shared__ int32_t hist_s[EP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i16 = lane & 15, g = lane >> 4;
+    const int64_t t0 = (int64_t)blockIdx.x * TM, t = t0 + i16 < T ? t0 + i16 : T - 1;
+    const XT *row = x + t * h;
+    f32x4 acc[NT];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc[j] = 0.f;
-        for (int k = lane; k < h; k += 64) {
-            float xv = x[t * h + k];
+    for (int n = 0; n < NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nsteps = (h + 15) / 16;
+    for (int s0 = wave; s0 < nsteps; s0 += NW * U) {
+        f32x4 a[U];
+        float b[U][NT][4];
+        // loads from clamped addresses, zeros selected afterwards: no branches between them
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
-                if (j0 + j < E) acc[j] = fmaf(xv, wg[(int64_t)k * E + j0 + j], acc[j]);
+        for (int u = 0; u < U; ++u) {
+            const int k = (s0 + NW * u) * 16 + 4 * g;
+            const bool in = k < h;
+            const int kc = in ? k : 0;
+            a[u] = load4(row + kc);
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                const int e = n * 16 + i16;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float w = wg[(int64_t)(kc + j) * E + (e < E ? e : 0)];
+                    b[u][n][j] = (in & (e < E)) ? w : 0.f;
+                }
+            }
+            if (!in) a[u] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            float v = acc[j];
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-            if (lane == 0 && j0 + j < E) logits[t * E + j0 + j] = v + (bias ? bias[j0 + j] : 0.f);
-        }
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int n = 0; n < NT; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][j], b[u][n][j], acc[n], 0, 0, 0);
     }
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[wave][g * 4 + v][n * 16 + i16] = acc[n][v];
+    __syncthreads();
+    for (int idx = tid; idx < TM * E; idx += 64 * NW) {
+        const int tt = idx / E, j = idx - tt * E;
+        float v = part[0][tt][j];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += part[w][tt][j];
+        if (bias) v += bias[j];
+        part[0][tt][j] = v;
+        if (t0 + tt < T) logits[(t0 + tt) * E + j] = v;
+    }
+    gate_choose<EP, TM, 64 * NW>(part[0], hist_s, probs, expert, gate_p, T, E, hist, token_of_slot, EC);
 }
 
 // softmax + top-1 from stored logits: 16 adjacent lanes per token, lane `sub` looks at experts sub, sub + 16, ...
@@ -392,6 +444,28 @@ static void launch_gate_bf16(const moe_shape_t *sh, const void *x, const bf16_t 
                        probs, expert, gate_p, sh->T, sh->h, sh->E, hist, token_of_slot, (int64_t)sh->E * sh->C);
 }
 
+template <typename XT>
+static void launch_gate_direct(const moe_shape_t *sh, int NT, const void *x, const float *wg, const float *bias,
+                               float *logits, float *probs, int32_t *expert, float *gate_p, int32_t *hist,
+                               int32_t *token_of_slot, hipStream_t s) {
+    const dim3 grid((unsigned)((sh->T + 15) / 16)), block(512);
+#define MOE_GATE_DIRECT(NT_, U_)                                                                                         \
+    hipLaunchKernelGGL((gate_direct_kernel<XT, NT_, U_>), grid, block, 0, s, (const XT *)x, wg, bias, logits, probs, expert, \
+                       gate_p, sh->T, sh->h, sh->E, hist, token_of_slot, (int64_t)sh->E * sh->C)
+    switch (NT) {
+        case 1: MOE_GATE_DIRECT(1, 8); break;
+        case 2: MOE_GATE_DIRECT(2, 4); break;
+        case 4: MOE_GATE_DIRECT(4, 2); break;
+        case 8: MOE_GATE_DIRECT(8, 1); break;
+        default: MOE_GATE_DIRECT(16, 1); break;
+    }
+#undef MOE_GATE_DIRECT
+}
+
+// bf16 tokens up to which gate_direct_kernel serves (whole moe_gate call, direct / planes): h = 2048, E = 16: 100 tokens
+// 14 / 22.6 us, 4096 tokens 17.3 / 24.4, 16384 tokens 39 / 27; E = 64: 4096 tokens 33 / 48, 8192 tokens 54 / 50
+constexpr int64_t GATE_DIRECT_TOKENS = 4096;
+
 moe_status_t run_gate(const moe_shape_t *sh, const void *x, const float *w_gate, const float *bias, float *logits,
                       float *probs, int32_t *expert, float *gate_p, int32_t *slot, int32_t *counts, int32_t *kept,
                       int32_t *token_of_slot, void *ws, hipStream_t s) {
@@ -405,10 +479,9 @@ moe_status_t run_gate(const moe_shape_t *sh, const void *x, const float *w_gate,
         hipLaunchKernelGGL(gate_softmax_top1_kernel, dim3((unsigned)((T * SM_TPT + 255) / 256)), dim3(256), 0, s, logits,
                            probs, expert, gate_p, T, sh->E);
     } else if (sh->dtype == MOE_F32) {
-        hipLaunchKernelGGL(gate_logits_f32_kernel, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, s, (const float *)x,
-                           w_gate, bias, logits, T, sh->h, sh->E);
-        hipLaunchKernelGGL(gate_softmax_top1_kernel, dim3((unsigned)((T * SM_TPT + 255) / 256)), dim3(256), 0, s, logits,
-                           probs, expert, gate_p, T, sh->E);
+        launch_gate_direct<float>(sh, NT, x, w_gate, bias, logits, probs, expert, gate_p, hist, token_of_slot, s);
+    } else if (sh->T <= GATE_DIRECT_TOKENS) {
+        launch_gate_direct<bf16_t>(sh, NT, x, w_gate, bias, logits, probs, expert, gate_p, hist, token_of_slot, s);
     } else {
         const int64_t n = (int64_t)NT * 16 * sh->h;
         hipLaunchKernelGGL(gate_split_wg_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w_gate, planes,
@@ -427,8 +500,8 @@ moe_status_t run_gate(const moe_shape_t *sh, const void *x, const float *w_gate,
     if (st != MOE_OK) return st;
     const unsigned nb = (unsigned)((T + RB - 1) / RB);
     int hist_block = RB;
-    if (x != nullptr && sh->dtype == MOE_BF16) {
-        hist_block = NT >= 8 ? 16 : 64;          // the gate kernel has written a histogram per workgroup (16 R tokens)
+    if (x != nullptr) {                          // the gate kernel has written a histogram per workgroup (16 R tokens)
+        hist_block = sh->dtype == MOE_F32 || sh->T <= GATE_DIRECT_TOKENS || NT >= 8 ? 16 : 64;
     } else {
         hipLaunchKernelGGL(route_hist_kernel, dim3(nb), dim3(RB), 0, s, expert, hist, token_of_slot, T, sh->E,
                            (int64_t)sh->E * sh->C);

@@ -52,7 +52,6 @@ struct AdamwConst {
 };
 moe_status_t run_adamw_tiled(int64_t, const AdamwConst &, const void *, float *, float *, float *, void *, int,
                              hipStream_t);
-moe_status_t run_gate_dx_f32(const moe_shape_t *, const float *, const float *, void *, hipStream_t);
 
 static size_t esize(const moe_shape_t *sh) { return sh->dtype == MOE_BF16 ? 2 : 4; }
 
@@ -582,11 +581,7 @@ moe_status_t moe_dispatch_bwd_dtd(const moe_shape_t *shape, const void *d_shares
         return MOE_ERR_INVALID_ARG;
     }
     if (d_logits == nullptr) return run_dispatch_bwd(shape, d_shares, expert, slot, d_x, (hipStream_t)stream, tp_size);
-    if (shape->dtype == MOE_BF16)
-        return run_dispatch_bwd_fused(shape, d_shares, expert, slot, d_x, d_logits, w_gate, (hipStream_t)stream, tp_size);
-    st = run_dispatch_bwd(shape, d_shares, expert, slot, d_x, (hipStream_t)stream, tp_size);
-    if (st != MOE_OK) return st;
-    return run_gate_dx_f32(shape, d_logits, w_gate, d_x, (hipStream_t)stream);
+    return run_dispatch_bwd_fused(shape, d_shares, expert, slot, d_x, d_logits, w_gate, (hipStream_t)stream, tp_size);
 }
 
 moe_status_t moe_combine(const moe_shape_t *shape, const void *y, const int32_t *expert, const int32_t *slot,
@@ -713,12 +708,7 @@ moe_status_t moe_dispatch_bwd(const moe_shape_t *shape, const void *d_buf, const
         return MOE_ERR_INVALID_ARG;
     }
     if (d_logits == nullptr) return run_dispatch_bwd(shape, d_buf, expert, slot, d_x, (hipStream_t)stream);
-    if (shape->dtype == MOE_BF16)
-        return run_dispatch_bwd_fused(shape, d_buf, expert, slot, d_x, d_logits, w_gate, (hipStream_t)stream);
-    // fp32 storage: plain row gather, then the gate part added in place
-    st = run_dispatch_bwd(shape, d_buf, expert, slot, d_x, (hipStream_t)stream);
-    if (st != MOE_OK) return st;
-    return run_gate_dx_f32(shape, d_logits, w_gate, d_x, (hipStream_t)stream);
+    return run_dispatch_bwd_fused(shape, d_buf, expert, slot, d_x, d_logits, w_gate, (hipStream_t)stream);
 }
 
 moe_status_t moe_gate_bwd(const moe_shape_t *shape, const float *d_gate_p, const float *probs, const int32_t *expert,

@@ -22,6 +22,17 @@ moe_status_t check_launch(const char *what);
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return (float)v; }
 __device__ __forceinline__ bf16_t f32_to_bf16(float v) { return (bf16_t)v; }   // round to nearest even
 
+// four consecutive elements, as fp32
+__device__ __forceinline__ f32x4 load4(const float *p) { return *(const f32x4 *)p; }
+__device__ __forceinline__ f32x4 load4(const bf16_t *p) {
+    const bf16x4 b = *(const bf16x4 *)p;
+    return f32x4{(float)b[0], (float)b[1], (float)b[2], (float)b[3]};
+}
+__device__ __forceinline__ void store4(float *p, const f32x4 &v) { *(f32x4 *)p = v; }
+__device__ __forceinline__ void store4(bf16_t *p, const f32x4 &v) {
+    *(bf16x4 *)p = bf16x4{(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
+}
+
 // ---- activation (exact erf form or tanh approximation), evaluated in fp32 ----
 __device__ __forceinline__ float act_fwd(float x, int act) {
     if (act == MOE_GELU_TANH) {

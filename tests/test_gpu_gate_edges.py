@@ -1,0 +1,46 @@
+"""The gate's kernels at the edges of their token blocks and expert tiles and on both sides of the token counts where
+one kernel hands over to another, against the CPU oracle.  Tolerances as in the other parity tests: fp32 logits 1e-5,
+gradients 1e-5 (fp32 storage) or 2e-2 (bf16 storage)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2303_06318_amd import moe, synth
+from gpu_util import DevInputs, host, make_layer, relfro, tol
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [
+    # T, h, E: one token; a token more than a block of 16, 64, 256; ragged columns; expert tiles of 16 and more
+    (1, 8, 1), (17, 72, 3), (65, 64, 16), (257, 136, 17), (1000, 264, 64), (1025, 200, 130), (300, 40, 256),
+    # hand-over of the bf16 kernels (128 and 1024 tokens; 4096 tokens; 2^22 and 2^21 values of x), each side
+    (1024, 72, 5), (1024, 4096, 16), (1025, 4096, 16), (128, 72, 33), (129, 72, 33), (1024, 2056, 34), (4096, 72, 33), (4097, 264, 16), (4160, 72, 65),
+]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,h,E", SIZES)
+def test_gate_edges(orc, T, h, E, dtype):
+    wl = synth.scaled(synth.WORKLOADS["cfg5_6p7b_tp4_fwdbwd"], T=T, h=h, f=8, E=E, capacity_factor=1.25, dtype=dtype, seed=3)
+    inp = synth.make_inputs(wl)
+    dev = DevInputs(inp)
+    layer = make_layer(wl, backward=True)
+    layer.forward(dev.x, dev.wg, dev.w1, dev.w2)
+    layer.backward(dev.d_out, dev.x, dev.wg, dev.w1, dev.w2)
+    torch.cuda.synchronize()
+    logits = host(layer.logits)
+    assert relfro(logits, orc.gate_logits(inp.x, inp.wg)) <= 1e-5
+    fw = orc.layer_forward(inp.x, inp.wg, inp.w1, inp.w2, wl.C, logits=logits)
+    bw = orc.layer_backward(fw, inp.d_out, inp.x, inp.wg, inp.w1, inp.w2)
+    for name in ("expert", "slot", "kept"):
+        assert np.array_equal(host(getattr(layer, name)), fw[name]), name
+    assert np.abs(host(layer.gate_p) - orc.top1_softmax(logits)[1]).max() <= 1e-5
+    t = tol(wl)
+    for name, o in (("d_logits", "dL"), ("d_w_gate", "dWg"), ("d_x", "dX")):
+        assert relfro(host(getattr(layer, name)), bw[o]) <= t, name
+
+    # the gate's term added in place gives what the fused dispatch backward gives, up to one more rounding of d_x
+    fused = host(layer.d_x).copy()
+    layer.backward(dev.d_out, dev.x, dev.wg, dev.w1, dev.w2, fused=False)
+    torch.cuda.synchronize()
+    assert relfro(host(layer.d_x), fused) <= (4e-3 if dtype == "bf16" else 1e-6)
