@@ -217,9 +217,11 @@ constexpr int DEEP_TILES = 256;
 //   capacity 200: 16 experts, 4096, 4096: 314 / 293;                  64 experts, 2048, 2048: 333 / 293
 //   capacity 250: 8 experts, 1024, 4096 (32 and 128 tiles): 64 / 130; 4 experts, 2048, 2048 (32 tiles): 43 / 105
 //   capacity 500: 4 experts, 2048, 2048 (64 tiles): 47 / 108;         capacity 1000 (128 tiles): 66 / 133
+//                 but 32 experts, 2768, 1096, first GEMM (160 tiles, one round of them; 576 of this kernel's tiles, two rounds
+//                 of the 512 that run at a time): 110 / 88, hence ROWS_SLOTS
 //   capacity 320: 4 experts, 4096, 8192 (128 and 256 tiles): 254 with this kernel for both, 231 for the first only
 constexpr int ROWS_MAX = 160;
-constexpr int ROWS_TILES = 255;
+constexpr int ROWS_TILES = 255, ROWS_SLOTS = 512;
 
 template <bool BXC, int EPI, int MB>
 static void launch_rows_mb(const GemmDesc &d, hipStream_t s) {
@@ -240,7 +242,8 @@ static void launch_rows(const GemmDesc &d, hipStream_t s) {
 
 bool gemm_rows_fits(const GemmDesc &d) {
     if (!d.rows_from_kept) return false;
-    return d.M <= ROWS_MAX || (int64_t)d.E * ((d.M + 287) / 288) * ((d.N + 255) / 256) <= ROWS_TILES;
+    return d.M <= ROWS_MAX || ((int64_t)d.E * ((d.M + 287) / 288) * ((d.N + 255) / 256) <= ROWS_TILES &&
+                               (int64_t)d.E * ((d.M + 127) / 128) * ((d.N + 127) / 128) <= ROWS_SLOTS);
 }
 
 moe_status_t launch_gemm_rows(const GemmDesc &d, hipStream_t s) {

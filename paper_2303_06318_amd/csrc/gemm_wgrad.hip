@@ -5,7 +5,7 @@
 // over a run of neighbouring 128 x 128 tiles of one row panel, requests run one k-tile ahead across tile ends
 // (straight into LDS, two stages), every wave writes its own 32 x 64 part through a private 2 KB of LDS as whole
 // 128-byte lines, and two workgroups share a compute unit (80 KB of LDS each; one workgroup with a ring of four
-// k-tiles was 6 % slower).  The results are stored past the caches: nothing reads them soon, and written through
+// k-tiles was 6 % slower).  Whole lines of the result are stored past the caches: nothing reads them soon, and written through
 // the L2 they displace the panels (16 experts x 100 rows, 4096 x 4096, whole backward: 606 -> 535 us).
 // Weight gradient of 16 experts of 4096 x 4096 with 6 rows each: 97 us for 537 MB (a fill of them takes 80).
 // Operand layouts, swizzles and the order of the sums are those of gemm_bf16.hip.
@@ -17,6 +17,7 @@ constexpr int WT = 128;                                      // tile edge
 constexpr int W_OPER = BK * WT * 2, W_STAGE = 2 * W_OPER;    // one operand's k-tile (16 KB)
 constexpr int W_OUT = 16 * 128;                              // a wave's staging area: 16 rows of 64 columns
 
+template <bool NT>
 __global__ __launch_bounds__(GEMM_THREADS, 4) void gemm_wgrad_kernel(GemmDesc d, int mt, int nt, int run, int runs, int total) {
     __shared__ __attribute__((aligned(1024))) char smem[2 * W_STAGE + 8 * W_OUT];
     const uint32_t smem_addr = (uint32_t)(uintptr_t)(lds_void *)smem;
@@ -105,23 +106,34 @@ __global__ __launch_bounds__(GEMM_THREADS, 4) void gemm_wgrad_kernel(GemmDesc d,
             for (int p = 0; p < 2; ++p) {
                 const int row = p * 8 + (lane >> 3), gm = m0 + wm + i * 16 + row, gn = n0 + (lane & 7) * 8;
                 const u32x4 v = *(const u32x4 *)(out + row * 128 + (((lane & 7) ^ (row & 7)) << 4));
-                if (gm < d.M && gn < d.N) __builtin_nontemporal_store(v, (u32x4 *)(C + (int64_t)gm * d.ldc + gn));
+                u32x4 *dst = (u32x4 *)(C + (int64_t)gm * d.ldc + gn);
+                if (gm < d.M && gn < d.N) {
+                    if constexpr (NT) __builtin_nontemporal_store(v, dst);
+                    else *dst = v;
+                }
             }
         }
     }
 }
 
+// Result rows that start on cache lines: every 128-byte piece a wave writes is a whole line and may bypass the caches.
+// Parts of lines are put together in the L2 (stored past it they cost a read each: 16 experts x 24 rows, 3000 x 4200,
+// whole backward 673 us, 509 with plain stores).
+static bool whole_lines(const GemmDesc &d) { return ((uintptr_t)d.C & 127) == 0 && d.ldc % 64 == 0; }
+
 // Where this kernel is chosen, against the kernel of gemm_bf16.hip (whole expert backward, this / the other; the
 // other one's 256 x 256 tiles in brackets):
-//   capacity up to 160:          16 experts x 100 rows, 2048 x 8192: 527 / 567 us; 64 x 48 rows, 2048 x 2048: 456 / 518;
-//                                from 200 on it loses where tiles are plenty (16 experts, 4096 x 4096 [4096]: 684 / 664 at 250)
+//   capacity up to 160, whole lines: 16 experts x 100 rows, 2048 x 8192: 527 / 567 us; 64 x 48 rows, 2048 x 2048: 456 / 518;
+//                                from 200 on it loses where tiles are plenty (16 experts, 4096 x 4096 [4096]: 684 / 664 at 250),
+//                                and so it does with parts of lines (32 experts, 1504 x 3304 [2496]: 383 / 351 at 30, 477 / 418
+//                                at 156), which the other kernel writes in pieces four times as long
 //   up to two tiles per unit:    8 experts, 1024 x 4096 [512]: 163 / 171 at capacity 500, 238 / 228 at 750
 //   up to one tile per unit:     4 experts, 2048 x 2048 [256]: 92 / 118 at capacity 500, 140 / 155 at 1000
 //   half of the units or fewer:  always
 bool gemm_wgrad_fits(const GemmDesc &d) {
     if (d.rows_from_kept) return false;
     const int64_t tiles = (int64_t)d.E * ((d.M + 255) / 256) * ((d.N + 255) / 256);
-    return d.K <= 160 || (d.K <= 512 && tiles <= 512) || (d.K <= 1024 && tiles <= 256) || tiles <= 128;
+    return (d.K <= 160 && whole_lines(d)) || (d.K <= 512 && tiles <= 512) || (d.K <= 1024 && tiles <= 256) || tiles <= 128;
 }
 
 moe_status_t launch_gemm_wgrad(const GemmDesc &d, hipStream_t s) {
@@ -134,7 +146,9 @@ moe_status_t launch_gemm_wgrad(const GemmDesc &d, hipStream_t s) {
     int run = 8;
     while (run > 1 && (int64_t)d.E * mt * ((nt + run - 1) / run) < 1024) run >>= 1;
     const int runs = (nt + run - 1) / run, total = d.E * mt * runs;
-    hipLaunchKernelGGL(gemm_wgrad_kernel, dim3((unsigned)((total + 7) / 8 * 8)), dim3(GEMM_THREADS), 0, s, d, mt, nt, run, runs, total);
+    const dim3 grid((unsigned)((total + 7) / 8 * 8)), block(GEMM_THREADS);
+    if (whole_lines(d)) hipLaunchKernelGGL(gemm_wgrad_kernel<true>, grid, block, 0, s, d, mt, nt, run, runs, total);
+    else hipLaunchKernelGGL(gemm_wgrad_kernel<false>, grid, block, 0, s, d, mt, nt, run, runs, total);
     return check_launch("gemm_wgrad");
 }
 

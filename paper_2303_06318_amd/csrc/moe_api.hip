@@ -236,7 +236,9 @@ static SideStream *side_stream(hipStream_t caller) {
 //   few rows:       16 experts x 48 rows, 4096 x 4096: 426 / 461 us; 64 x 6 rows, 2048 x 2048: 412 / 435 (100 rows: 605 / 561)
 //   small weights:  32 x 100 rows, 1024 x 1024: 70 / 79; 4 x 6 rows, 2048 x 2048: 43 / 58; 8 x 100 rows, 1024 x 4096: 90 / 91
 //                   (200 rows: 107 / 104)
-static bool bwd_one_stream(const moe_shape_t &s) {
+// and only where the weight gradients have the kernel for few rows (32 x 60 rows, 2768 x 1096, without: 280 / 254).
+static bool bwd_one_stream(const moe_shape_t &s, const GemmDesc &dw2, const GemmDesc &dw1) {
+    if (!gemm_wgrad_fits(dw2) || !gemm_wgrad_fits(dw1)) return false;
     return s.C <= 64 || (s.C <= 160 && (int64_t)s.E * s.h * s.f <= ((int64_t)1 << 25));
 }
 
@@ -663,7 +665,7 @@ moe_status_t moe_expert_ffn_bwd(const moe_shape_t *shape, const void *d_y, const
         for (int i = 0; i < 4; ++i) { g[i].plan = pl; pl += gemm_bf16_plan_bytes(g[i]); }
         if ((st = launch_gemm_bf16_plans(g, 4, hs)) != MOE_OK) return st;
     }
-    SideStream *ss = bf && !bwd_one_stream(s) ? side_stream(hs) : nullptr;
+    SideStream *ss = bf && !bwd_one_stream(s, g[1], g[2]) ? side_stream(hs) : nullptr;
     if (ss == nullptr) {     // one after the other
         for (int i = 0; i < 4; ++i)
             if ((st = bf ? launch_gemm_bf16(g[i], hs) : launch_gemm_f32(g[i], hs)) != MOE_OK) return st;
