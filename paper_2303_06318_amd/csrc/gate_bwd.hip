@@ -400,8 +400,8 @@ __global__ __launch_bounds__(256) void gate_dx_kernel(const float *w_gate, const
 // leading products summed in fp32.  LDS only holds the workgroup's small operands (source row of each
 // token, d_logits rows), written once before the loop, so that the loop's only vector-memory traffic is
 // the row stream.
-constexpr int DX_TOKENS = 192;          // tokens per workgroup (4 waves x 128 columns each); a multiple of 48
-template <int KS, bool GATHER>          // 32-expert k-steps (E <= 32 KS); rows gathered from d_buf, or d_x in place
+// DX_TOKENS: tokens per workgroup (4 waves x 128 columns each); a multiple of 48
+template <int KS, bool GATHER, int DX_TOKENS>          // 32-expert k-steps (E <= 32 KS); rows gathered from d_buf, or d_x in place
 __global__ __launch_bounds__(256, KS == 1 ? 2 : 1) void gate_dx_rows_kernel(
     const float *w_gate, const float *d_logits, bf16_t *d_x, int64_t T, int h, int E, const bf16_t *d_buf,
     const int32_t *expert, const int32_t *slot, int64_t Cg, int G) {
@@ -685,36 +685,44 @@ static void launch_dx(const moe_shape_t *sh, const float *w_gate, const float *d
 static bool dx_rows_ok(const moe_shape_t *sh, int tp_size = 1) {
     const double src_rows = (double)tp_size * sh->E * (double)((sh->C + tp_size - 1) / tp_size);
     return sh->E <= 64 && src_rows * sh->h * 2.0 < 2147483648.0 && (double)sh->T * sh->h * 2.0 < 2147483648.0 &&
-           (sh->T + DX_TOKENS - 1) / DX_TOKENS <= 65535;      // one workgroup row per DX_TOKENS tokens in the grid's second dimension
+           (sh->T + 191) / 192 <= 65535;      // one workgroup row per 192 tokens (fewer only while there are few) in the grid's second dimension
 }
 
+// Workgroups to have before chunks of tokens get longer: with more experts a chunk has more Wg^T to amortise.  Chunks by
+// this rule / always 192 tokens: h = 2048, E = 16: 6000 tokens 14.7 / 19.6 us, 8192 tokens 17.7 / 21.2; h = 2768, E = 32:
+// 6000 tokens 23.3 / 27.2; E = 64: h = 2048, 4096 tokens 37.0 / 41.4, h = 4096, 4096 tokens 43.8 (192 by the rule; 57.8 by 48)
+static int64_t dx_fill(int E) { return E <= 16 ? 512 : E <= 32 ? 256 : 128; }
+// A workgroup = 4 waves = 512 columns of one chunk of TOK tokens; a long chunk amortises the Wg^T fragments (128 columns
+// x E floats per wave), a short one gives every compute unit several workgroups.
+template <int KS, bool GATHER, int TOK>
+static void launch_dx_rows(const moe_shape_t *sh, const float *w_gate, const float *d_logits, void *d_x, hipStream_t s,
+                           const void *d_buf, const int32_t *expert, const int32_t *slot, int tp_size) {
+    const dim3 grid((unsigned)((sh->h + 511) / 512), (unsigned)((sh->T + TOK - 1) / TOK));
+    const int E8 = (sh->E + 7) & ~7;
+    const size_t lds = (size_t)512 * (E8 + 4) * 4 + (TOK + 48) * 4;
+    static_assert(TOK + 16 <= 512, "the d_logits rows reuse the 512-row region");
+    if (lds > 65536)        // more than 64 KB of dynamic LDS has to be allowed per kernel (E > 32: up to 139 KB)
+        (void)hipFuncSetAttribute((const void *)gate_dx_rows_kernel<KS, GATHER, TOK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((gate_dx_rows_kernel<KS, GATHER, TOK>), grid, dim3(256), lds, s, w_gate, d_logits, (bf16_t *)d_x, sh->T,
+                       sh->h, sh->E, (const bf16_t *)d_buf, expert, slot, (sh->C + tp_size - 1) / tp_size, tp_size);
+}
+template <int KS, bool GATHER>
+static void launch_dx_chunks(const moe_shape_t *sh, const float *w_gate, const float *d_logits, void *d_x, hipStream_t s,
+                             const void *d_buf, const int32_t *expert, const int32_t *slot, int tp_size) {
+    const int64_t cols = (sh->h + 511) / 512, fill = dx_fill(sh->E);
+    if (cols * ((sh->T + 191) / 192) >= fill)
+        launch_dx_rows<KS, GATHER, 192>(sh, w_gate, d_logits, d_x, s, d_buf, expert, slot, tp_size);
+    else if (cols * ((sh->T + 95) / 96) >= fill)
+        launch_dx_rows<KS, GATHER, 96>(sh, w_gate, d_logits, d_x, s, d_buf, expert, slot, tp_size);
+    else
+        launch_dx_rows<KS, GATHER, 48>(sh, w_gate, d_logits, d_x, s, d_buf, expert, slot, tp_size);
+}
 static void launch_dx_mfma(const moe_shape_t *sh, const float *w_gate, const float *d_logits, void *d_x, hipStream_t s,
                            const void *d_buf = nullptr, const int32_t *expert = nullptr, const int32_t *slot = nullptr,
                            int tp_size = 1) {
-    // a workgroup = 4 waves = 512 columns of one chunk of DX_TOKENS tokens; the chunk amortises the Wg^T
-    // fragments (128 columns x E floats per wave) and is short enough to give every compute unit several workgroups
-    dim3 grid((unsigned)((sh->h + 511) / 512), (unsigned)((sh->T + DX_TOKENS - 1) / DX_TOKENS));
-    const int E8 = (sh->E + 7) & ~7;
-    const size_t lds = (size_t)512 * (E8 + 4) * 4 + (DX_TOKENS + 48) * 4;       // 512 >= DX_TOKENS + 16 rows
-    static_assert(DX_TOKENS + 16 <= 512, "the d_logits rows reuse the 512-row region");
-    // more than 64 KB of dynamic LDS has to be allowed per kernel (E > 32: up to 139 KB)
-#define MOE_DX_ROWS(KS, GATHER)                                                                                      \
-    do {                                                                                                             \
-        if (lds > 65536)                                                                                             \
-            (void)hipFuncSetAttribute((const void *)gate_dx_rows_kernel<KS, GATHER>,                                 \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                        \
-        hipLaunchKernelGGL((gate_dx_rows_kernel<KS, GATHER>), grid, dim3(256), lds, s, w_gate, d_logits,             \
-                           (bf16_t *)d_x, sh->T, sh->h, sh->E, (const bf16_t *)d_buf, expert, slot,                  \
-                           (sh->C + tp_size - 1) / tp_size, tp_size);                                                \
-    } while (0)
-    if (d_buf) {
-        if (sh->E <= 32) MOE_DX_ROWS(1, true);
-        else MOE_DX_ROWS(2, true);
-    } else {
-        if (sh->E <= 32) MOE_DX_ROWS(1, false);
-        else MOE_DX_ROWS(2, false);
-    }
-#undef MOE_DX_ROWS
+    auto launch = d_buf ? (sh->E <= 32 ? launch_dx_chunks<1, true> : launch_dx_chunks<2, true>)
+                        : (sh->E <= 32 ? launch_dx_chunks<1, false> : launch_dx_chunks<2, false>);
+    launch(sh, w_gate, d_logits, d_x, s, d_buf, expert, slot, tp_size);
 }
 
 template <typename XT>

@@ -12,7 +12,8 @@
 // which every block of 1024 tokens adds up the histograms of the tokens before it (all threads in
 // parallel, integer atomics again), ranks its own tokens with wave ballots (token order inside a wave
 // = lane order) and writes slot / token_of_slot; the last block writes counts and kept.
-#include "moe_common.h"
+#include <type_traits>
+#include "gemm_bf16_parts.h"
 
 namespace moe {
 
@@ -85,8 +86,116 @@ __device__ __forceinline__ void gate_choose(const float (*lg)[EP + 1], int32_t *
     for (int64_t i = i0 + tid; i < i0 + per && i < EC; i += THREADS) token_of_slot[i] = -1;
 }
 
-// ------------------------------------------------------------------ fused gate, bf16 tokens
-// Workgroup: NW waves, 16*R tokens.  Wave w takes k-steps w, w+NW, ... (32 k each); the NW partial
+// ------------------------------------------------------------------ fused gate, bf16 tokens, up to 64 experts
+// A workgroup of 4 waves takes 64 tokens; x and the planes of Wg go straight into LDS in k-tiles of 64 through a ring
+// of S stages (the loaders of the grouped GEMMs); a wave multiplies 16 NT tokens with one of the NT expert tiles.
+// Bound by the path from the L2 into the compute unit, about 29 cycles per KB when every request covers whole 128-byte
+// lines.  MFMA fragments loaded from memory directly are requests of 64 bytes out of 16 rows each, at twice that per
+// KB.  Whole moe_gate call, 16384 tokens, with fragments from memory / now: h = 4096, E = 16:
+// 38.5 / 32.9 us; h = 2048, E = 64: 52.6 / 46.0.
+// The sums of the high planes run in four chains (k-step parity x k-tile parity), those of the other planes in a
+// chain of their own, so that fewer roundings at the size of the result follow each other than with one chain.
+template <int NT, int S>
+__global__ __launch_bounds__(256) void gate_stream_kernel(const bf16_t *x, const bf16_t *planes, const float *bias,
+                                                          float *logits, float *probs, int32_t *expert, float *gate_p,
+                                                          int64_t T, int h, int E, int32_t *hist, int32_t *token_of_slot,
+                                                          int64_t EC) {
+    constexpr int EP = NT * 16, TM = 64, PQ = (6 * NT + 3) / 4, L = 2 + PQ;      // 1 KB requests of a wave per k-tile: 2 of x, PQ of the planes
+    constexpr int X_BYTES = TM * KC_ROW, STAGE = X_BYTES + PQ * 4096;
+    static_assert(TM * (EP + 1) * 4 <= S * STAGE, "the logits are staged in the operand stages");
+    __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
+    __shared__ int32_t hist_s[EP];
+    const uint32_t smem_addr = (uint32_t)(uintptr_t)(lds_void *)smem;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t t0 = (int64_t)blockIdx.x * TM;
+    const int rows = (int)(T - t0 < TM ? T - t0 : TM);
+    const i32x4 X = make_rsrc(x + t0 * h, (uint32_t)rows * (uint32_t)h * 2u);
+    const i32x4 P = make_rsrc(planes, (uint32_t)(3 * EP) * (uint32_t)h * 2u);
+    Loader<false, 2, 128, 4> lx;
+    Loader<false, PQ, 128, 4> lp;
+    lx.init(h, 0, rows, wave, lane);
+    lp.init(h, 0, 3 * EP, wave, lane);
+    lx.init_k(h, wave, lane);
+    lp.kthr = lx.kthr;
+    FragAddr<false, 128> fx, fp;
+    const int wn = wave % NT, wm = wave / NT * NT;               // the wave's expert tile and first 16-token block (of NT)
+    fx.init(wm * 16, lane);
+    fp.init(wn * 16, lane);
+    auto request = [&](int kt, int stage) {                      // past the end of h: zeros, without memory traffic
+        const uint32_t base = smem_addr + stage * STAGE + wave * 1024;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) lx.request(X, base, kt * BK, h, q);
+#pragma unroll
+        for (int q = 0; q < PQ; ++q) lp.request(P, base + X_BYTES, kt * BK, h, q);
+    };
+    f32x4 hi[4][NT], low[NT];
+#pragma unroll
+    for (int r = 0; r < NT; ++r) {
+        low[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) hi[c][r] = low[r];
+    }
+    const int nk = (h + BK - 1) / BK;
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s) request(s, s);
+    int stage = 0;
+    auto k_tile = [&](int kt, auto parity) {
+        // k-tile kt has landed (S - 2 newer ones may be outstanding), and every wave has read k-tile kt - 1, whose
+        // stage the next request overwrites
+        constexpr int N = (S - 2) * L;
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | (N >> 4) << 14);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        request(kt + S - 1, stage == 0 ? S - 1 : stage - 1);
+        const char *tx = smem + stage * STAGE, *tp = tx + X_BYTES;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            bf16x8 a[NT], b[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) b[p] = fp.read(tp, p * NT, ks);
+#pragma unroll
+            for (int r = 0; r < NT; ++r) a[r] = fx.read(tx, r, ks);
+#pragma unroll
+            for (int r = 0; r < NT; ++r) {
+                f32x4 &c = hi[2 * decltype(parity)::value + ks][r];
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[0], c, 0, 0, 0);
+                low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[1], low[r], 0, 0, 0);
+                low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[2], low[r], 0, 0, 0);
+            }
+        }
+        stage = stage == S - 1 ? 0 : stage + 1;
+    };
+    for (int kt = 0; kt < nk; kt += 2) {
+        k_tile(kt, std::integral_constant<int, 0>{});
+        if (kt + 1 < nk) k_tile(kt + 1, std::integral_constant<int, 1>{});
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0070);                          // nothing may still be writing LDS when it is reused
+    __syncthreads();
+    // 16x16 result: lane holds column (expert) lane%16, rows (tokens) 4*(lane/16) + v
+    float(*lg)[EP + 1] = (float(*)[EP + 1])smem;
+#pragma unroll
+    for (int r = 0; r < NT; ++r)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            lg[(wm + r) * 16 + (lane >> 4) * 4 + v][wn * 16 + (lane & 15)] = ((hi[0][r][v] + hi[1][r][v]) + (hi[2][r][v] + hi[3][r][v])) + low[r][v];
+    __syncthreads();
+    for (int idx = tid; idx < TM * E; idx += 256) {
+        const int tt = idx / E, j = idx - tt * E;
+        float v = lg[tt][j];
+        if (bias) v += bias[j];
+        lg[tt][j] = v;
+        if (t0 + tt < T) logits[(t0 + tt) * E + j] = v;
+    }
+    gate_choose<EP, TM, 256>(lg, hist_s, probs, expert, gate_p, T, E, hist, token_of_slot, EC);
+}
+
+// ------------------------------------------------------------------ fused gate, bf16 tokens, more experts
+// (their planes do not fit a ring of k-tiles in LDS)
+// Workgroup: NW waves, 16*R tokens.  Of every NW*U k-steps (32 k each) wave w takes the U from w*U on: two k-steps are
+// the 128-byte cache line of a row, which so goes to one wave (dealt out singly, every line came from the L2 into the
+// compute unit twice, and that path is what bounds the kernel).  The NW partial
 // [16R x Epad] tiles are summed through LDS in a fixed order.  The three planes of Wg are read from
 // L2 once per workgroup, so R is chosen large enough that this traffic stays below that of X.
 template <int NT, int R, int NW, int U>
@@ -211,7 +320,7 @@ __global__ __launch_bounds__(64 * NW) void gate_bf16_kernel(const bf16_t *x, con
 // The whole gate of 16 tokens per workgroup on v_mfma_f32_16x16x4_f32, for fp32 tokens, and for bf16 tokens while
 // there are few of them: Wg is used as it is stored, without planes and the launch that makes them, and 16 tokens
 // per workgroup spread a short token tensor over four times as many compute units as 64 do.
-// The 8 waves split the reduction (16 k per step, U steps in flight); lane l supplies token l % 16 and expert l % 16
+// The 8 waves split the reduction (16 k per step, U consecutive steps in flight: whole cache lines of x); lane l supplies token l % 16 and expert l % 16
 // with k = 4 (l / 16) + j to the j-th of four instructions.  A launch-latency kernel: fp32, 2048 tokens, h = 1024, E = 8:
 // 42 us for the whole moe_gate call with vector FMAs, a softmax kernel and a histogram kernel, now 11.7.
 template <typename XT, int NT, int U>
@@ -228,13 +337,13 @@ __global__ __launch_bounds__(512) void gate_direct_kernel(const XT *x, const flo
 #pragma unroll
     for (int n = 0; n < NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int nsteps = (h + 15) / 16;
-    for (int s0 = wave; s0 < nsteps; s0 += NW * U) {
+    for (int s0 = wave * U; s0 < nsteps; s0 += NW * U) {
         f32x4 a[U];
         float b[U][NT][4];
         // loads from clamped addresses, zeros selected afterwards: no branches between them
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = (s0 + NW * u) * 16 + 4 * g;
+            const int k = (s0 + u) * 16 + 4 * g;
             const bool in = k < h;
             const int kc = in ? k : 0;
             a[u] = load4(row + kc);
@@ -455,15 +564,16 @@ static void launch_gate_direct(const moe_shape_t *sh, int NT, const void *x, con
     switch (NT) {
         case 1: MOE_GATE_DIRECT(1, 8); break;
         case 2: MOE_GATE_DIRECT(2, 4); break;
-        case 4: MOE_GATE_DIRECT(4, 2); break;
+        case 4: MOE_GATE_DIRECT(4, 4); break;
         case 8: MOE_GATE_DIRECT(8, 1); break;
         default: MOE_GATE_DIRECT(16, 1); break;
     }
 #undef MOE_GATE_DIRECT
 }
 
-// bf16 tokens up to which gate_direct_kernel serves (whole moe_gate call, direct / planes): h = 2048, E = 16: 100 tokens
-// 14 / 22.6 us, 4096 tokens 17.3 / 24.4, 16384 tokens 39 / 27; E = 64: 4096 tokens 33 / 48, 8192 tokens 54 / 50
+// bf16 tokens up to which gate_direct_kernel serves, one workgroup per compute unit (whole moe_gate call, direct / stream):
+// h = 2048, E = 16: 2048 tokens 14.0 / 19.8 us, 4096 tokens 15.4 / 19.6, 6000 tokens 21.8 / 20.4; E = 64: 4096 tokens
+// 33 / 40, 6000 tokens 48 / 44
 constexpr int64_t GATE_DIRECT_TOKENS = 4096;
 
 moe_status_t run_gate(const moe_shape_t *sh, const void *x, const float *w_gate, const float *bias, float *logits,
@@ -486,15 +596,18 @@ moe_status_t run_gate(const moe_shape_t *sh, const void *x, const float *w_gate,
         const int64_t n = (int64_t)NT * 16 * sh->h;
         hipLaunchKernelGGL(gate_split_wg_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w_gate, planes,
                            sh->h, sh->E, NT * 16);
-        // template arguments: 16-expert tiles, tokens per workgroup / 16, waves, k-steps per batch (two batches in
-        // flight per wave: 2 U (R + 3 NT) fragments of 4 registers)
+#define MOE_GATE_STREAM(NT_, S_)                                                                                              \
+    hipLaunchKernelGGL((gate_stream_kernel<NT_, S_>), dim3((unsigned)((T + 63) / 64)), dim3(256), 0, s, (const bf16_t *)x, planes, \
+                       bias, logits, probs, expert, gate_p, T, sh->h, sh->E, hist, token_of_slot, (int64_t)sh->E * sh->C)
+        // launch_gate_bf16: 16-expert tiles, tokens per workgroup / 16, waves, k-steps per batch
         switch (NT) {
-            case 1: launch_gate_bf16<1, 4, 8, 2>(sh, x, planes, bias, logits, probs, expert, gate_p, hist, token_of_slot, s); break;
-            case 2: launch_gate_bf16<2, 4, 8, 2>(sh, x, planes, bias, logits, probs, expert, gate_p, hist, token_of_slot, s); break;
-            case 4: launch_gate_bf16<4, 4, 8, 1>(sh, x, planes, bias, logits, probs, expert, gate_p, hist, token_of_slot, s); break;
+            case 1: MOE_GATE_STREAM(1, 4); break;
+            case 2: MOE_GATE_STREAM(2, 4); break;
+            case 4: MOE_GATE_STREAM(4, 4); break;
             case 8: launch_gate_bf16<8, 1, 4, 1>(sh, x, planes, bias, logits, probs, expert, gate_p, hist, token_of_slot, s); break;
             default: launch_gate_bf16<16, 1, 4, 1>(sh, x, planes, bias, logits, probs, expert, gate_p, hist, token_of_slot, s); break;
         }
+#undef MOE_GATE_STREAM
     }
     moe_status_t st = check_launch("gate");
     if (st != MOE_OK) return st;

@@ -92,18 +92,19 @@ struct RowMap {
 };
 
 // Global -> LDS copy of one operand.  A part of a tile (a half of A, the whole of B) is filled by 1 KB
-// chunks, chunk wave + 8 q by wave `wave`; lane L fills granule L of the chunk:
+// chunks, chunk wave + WAVES q by wave `wave`; lane L fills granule L of the chunk:
 //   KC chunk:   8 rows of 128 bytes,    lane L -> row L / 8,    position L % 8
 //   XC A chunk: 4 k-rows of 256 bytes,  lane L -> k-row L / 16, position L % 16
 //   XC B chunk: 2 k-rows of 512 bytes,  lane L -> k-row L / 32, position L % 32
-// Chunks of a wave are 8 apart, so the swizzle of a lane is the same in all of them, and in an XC operand
-// they differ by a whole number of k-rows, which goes into the load's scalar offset: one offset register
-// per part, whereas the rows of a KC operand are bounds-checked (or gathered) one by one.
-template <bool XC, int NQ, int XC_COLS>
+// Chunks of a wave are 8 (or, in workgroups of 4 waves, 4) apart, so the swizzle of a lane is the same in all of them,
+// and in an XC operand they differ by a whole number of k-rows, which goes into the load's scalar offset: one offset
+// register per part, whereas the rows of a KC operand are bounds-checked (or gathered) one by one.
+template <bool XC, int NQ, int XC_COLS, int WAVES = 8>
 struct Loader {
+    static_assert(WAVES == 8 || (WAVES == 4 && (!XC || XC_COLS == 128)), "chunks of a wave share one swizzle");
     static constexpr int KROWS = 1024 / (XC_COLS * 2);      // XC: k-rows per chunk
     uint32_t off[XC ? 1 : NQ];           // byte offset of this lane's granule at k = 0 (OOB: outside the operand in x)
-    int32_t kthr;                        // the granule of chunk q is below klim iff k0 (XC: + q * 8 * KROWS) < kthr
+    int32_t kthr;                        // the granule of chunk q is below klim iff k0 (XC: + q * WAVES * KROWS) < kthr
     __device__ __forceinline__ void init_k(int klim, int wave, int lane) {
         if (XC) kthr = klim - (wave * KROWS + lane / (64 / KROWS));
         else kthr = klim - (((lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7)) << 3);
@@ -117,7 +118,7 @@ struct Loader {
         } else {
 #pragma unroll
             for (int q = 0; q < (XC ? 1 : NQ); ++q) {
-                const int row = (wave + 8 * q) * 8 + (lane >> 3);
+                const int row = (wave + WAVES * q) * 8 + (lane >> 3);
                 const int g = (lane & 7) ^ ((row >> 1) & 7);
                 const int gx = x0 + row;
                 if (map.mapped()) {
@@ -129,11 +130,11 @@ struct Loader {
             }
         }
     }
-    // request chunk q of the part's k-tile at origin k0 (it lands at lds + q * 8 KB); past the end of K: zeros
+    // request chunk q of the part's k-tile at origin k0 (it lands at lds + q * WAVES KB); past the end of K: zeros
     __device__ __forceinline__ void request(const i32x4 &rsrc, uint32_t lds, int k0, int ld, int q) const {
-        const int k = XC ? k0 + q * 8 * KROWS : k0;
+        const int k = XC ? k0 + q * WAVES * KROWS : k0;
         const uint32_t voff = k < kthr ? off[XC ? 0 : q] : OOB;
-        load_to_lds(rsrc, lds + q * 8192, voff, XC ? (uint32_t)k * ld * 2u : (uint32_t)k * 2u);
+        load_to_lds(rsrc, lds + q * WAVES * 1024, voff, XC ? (uint32_t)k * ld * 2u : (uint32_t)k * 2u);
     }
 };
 
