@@ -137,8 +137,9 @@ template <int EPI, bool AXC, bool BXC>
 static void launch_f32(const GemmDesc &d, hipStream_t s) {
     // Wide tiles from four per compute unit on.  Forward pair of GEMMs, wide / narrow: 32 tiles 17.5 / 11.8 us,
     // 192 tiles 37 / 26, 384 tiles 93 / 69, 640 tiles 129 / 111; with weight gradients of 2048 tiles the backward
-    // takes 144 / 155.
-    const bool w = (int64_t)((d.N + 63) / 64) * ((d.M + 63) / 64) * d.E >= 1024;
+    // takes 144 / 155.  Weight gradients, whose reduction is short, from one per compute unit on (whole backward with
+    // 256 tiles 34.4 / 37.3, with 512 tiles 49.5 / 55.1).
+    const bool w = (int64_t)((d.N + 63) / 64) * ((d.M + 63) / 64) * d.E >= (AXC ? 256 : 1024);
     const int t = w ? 64 : 32;
     const dim3 grid((d.N + t - 1) / t, (d.M + t - 1) / t, d.E);
     if (w) hipLaunchKernelGGL((gemm_f32_kernel<EPI, AXC, BXC, true>), grid, dim3(F32_THREADS), 0, s, d);
