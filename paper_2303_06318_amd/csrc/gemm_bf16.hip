@@ -274,7 +274,6 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmDesc d) {
     if (tile_idx < 0) break;
     const int ent0 = __builtin_amdgcn_readfirstlane(s_next[0]);
     const int e = ent0 & 255, nblk = (ent0 >> 8) & 15;
-    const bool light = (ent0 >> 12) & 1;
     const int nti = __builtin_amdgcn_readfirstlane(s_next[1]);
     const int blk0 = __builtin_amdgcn_readfirstlane(s_next[2]);
     const int kept = __builtin_amdgcn_readfirstlane(s_next[3]);
