@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmoe_ted.so")
 SOURCES = ["moe_api.hip", "gate_route.hip", "permute.hip", "gate_bwd.hip", "gemm_f32.hip", "gemm_bf16.hip", "gemm_rows.hip", "gemm_wgrad.hip",
-           "adamw.hip"]
+           "gemm_panel.hip", "adamw.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 

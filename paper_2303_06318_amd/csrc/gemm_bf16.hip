@@ -736,7 +736,7 @@ moe_status_t launch_gemm_bf16_plans(const GemmDesc *descs, int n, hipStream_t s)
     int np = 0;
     for (int i = 0; i < n; ++i) {
         const GemmDesc &d = descs[i];
-        if (gemm_rows_fits(d) || gemm_wgrad_fits(d)) continue;
+        if (gemm_rows_fits(d) || gemm_panel_fits(d) || gemm_wgrad_fits(d)) continue;
         if (d.plan == nullptr || d.E > 256) {
             set_error("gemm_bf16: no plan buffer, or more than 256 experts");
             return MOE_ERR_INVALID_ARG;
@@ -762,6 +762,7 @@ static void launch_one(const GemmDesc &d, hipStream_t s) {
 // for this descriptor's kept, E, M, N, K, rows_from_kept and A layout; a plan serves one launch.
 moe_status_t launch_gemm_bf16(const GemmDesc &d, hipStream_t s) {
     if (gemm_rows_fits(d)) return launch_gemm_rows(d, s);
+    if (gemm_panel_fits(d)) return launch_gemm_panel(d, s);
     if (gemm_wgrad_fits(d)) return launch_gemm_wgrad(d, s);
     if (d.plan == nullptr) {
         set_error("gemm_bf16: no plan");

@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <mutex>
 #include "moe_common.h"
+#include "kernel_choice.h"
 
 namespace moe {
 
@@ -236,8 +237,11 @@ static SideStream *side_stream(hipStream_t caller) {
 //   few rows:       16 experts x 48 rows, 4096 x 4096: 426 / 461 us; 64 x 6 rows, 2048 x 2048: 412 / 435 (100 rows: 605 / 561)
 //   small weights:  32 x 100 rows, 1024 x 1024: 70 / 79; 4 x 6 rows, 2048 x 2048: 43 / 58; 8 x 100 rows, 1024 x 4096: 90 / 91
 //                   (200 rows: 107 / 104)
-// and only where the weight gradients have the kernel for few rows (32 x 60 rows, 2768 x 1096, without: 280 / 254).
+// and only where the weight gradients have a kernel for few rows (32 x 60 rows, 2768 x 1096, without: 280 / 254).  From
+// panels (gemm_panel.hip) also up to 160 rows, where their workgroups fill the chip to the end.
 static bool bwd_one_stream(const moe_shape_t &s, const GemmDesc &dw2, const GemmDesc &dw1) {
+    if (gemm_panel_fits(dw2) && gemm_panel_fits(dw1) && s.C <= 160)
+        return s.C <= 64 || (gemm_panel_fills(s.E, dw2.M, dw2.N, dw2.K) && gemm_panel_fills(s.E, dw1.M, dw1.N, dw1.K));
     if (!gemm_wgrad_fits(dw2) || !gemm_wgrad_fits(dw1)) return false;
     return s.C <= 64 || (s.C <= 160 && (int64_t)s.E * s.h * s.f <= ((int64_t)1 << 25));
 }

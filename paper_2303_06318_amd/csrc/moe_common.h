@@ -96,5 +96,7 @@ bool gemm_rows_fits(const GemmDesc &d);                 // forward and data-grad
 moe_status_t launch_gemm_rows(const GemmDesc &d, hipStream_t s);
 bool gemm_wgrad_fits(const GemmDesc &d);                // weight gradients
 moe_status_t launch_gemm_wgrad(const GemmDesc &d, hipStream_t s);
+bool gemm_panel_fits(const GemmDesc &d);                // weight gradients of large matrices, before the one above
+moe_status_t launch_gemm_panel(const GemmDesc &d, hipStream_t s);
 
 }  // namespace moe
