@@ -128,6 +128,7 @@ static GemmDesc ffn_gemm(const moe_shape_t &s, int which) {
     GemmDesc g = {};
     g.E = s.E; g.act = s.act; g.epi = EPI_STORE;
     const int32_t C = (int32_t)s.C;
+    g.rows = (int32_t)((s.T + s.E - 1) / s.E < s.C ? (s.T + s.E - 1) / s.E : s.C);
     switch (which) {
         case G_FWD1:   // z = buf w1, hact = act(z)        A = buf [M,h], B = w1 [h,f] = [K,N]
             g.strideA = s.C * s.h; g.strideB = (int64_t)s.h * s.f; g.strideC = s.C * s.f;

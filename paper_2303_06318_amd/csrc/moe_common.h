@@ -65,6 +65,7 @@ struct GemmDesc {
     const int32_t *kept;
     int64_t strideA, strideB, strideC;   // elements between experts
     int32_t M, N, K;                     // upper bounds / fixed sizes
+    int32_t rows;                        // what an expert holds when the tokens spread evenly, for the choice of a kernel only
     int32_t lda, ldb, ldc;
     int32_t E;
     int32_t a_xc, b_xc, rows_from_kept, epi, act;

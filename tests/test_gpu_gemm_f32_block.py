@@ -1,0 +1,56 @@
+"""The block form of the fp32 grouped GEMM (tiles of up to 160 x 64 on 16 x 16 x 4 MFMAs) at the edges of its tiles, against
+the CPU oracle; tolerance as for every fp32 parity test (1e-5 per row and tile).  Experts hold no rows or at least six: a row of d_w2
+is a sum over the expert's rows of hact times d_y, and where a single hact is next to zero (its z is a sum of 512 products with a
+rounding error of 1e-7, whatever computes it) that row's own norm measures nothing."""
+import pytest
+
+from kernel_choice import choice
+from test_gpu_gemm_edges import run_rows
+
+NARROW, WIDE, BLOCK = range(3)
+
+
+def forms(E, rows, h, f):
+    """(row blocks of a tile, alone on its unit) of GEMM1 / dH and of GEMM2 / dD, form of the weight gradients"""
+    r, R = choice(), min(-(-sum(rows) // E), max(rows))
+    return [(p >> 1, bool(p & 1)) for p in (r.f32_plan(E, R, f, h), r.f32_plan(E, R, h, f))], r.f32_wgrad_form(E, h, f, R)
+
+
+def fill(E, rows, rest):
+    return tuple(rows) + tuple(rest[i % len(rest)] for i in range(E - len(rows)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("E,rows,h,f,want,wgrad", [
+    # one tile per unit, five blocks: ragged columns and k-tiles; 8 to 10 and 16 to 20 row blocks
+    (8, (320, 272, 257, 256, 241, 240, 160, 161), 1024, 1020, [(5, True), (5, True)], BLOCK),
+    # two workgroups per unit; experts without rows, with one, with partial blocks
+    (64, fill(64, (160, 161, 320, 0, 6, 15, 16, 17, 33, 0), (130, 128, 97)), 512, 516, [(3, False), (5, False)], WIDE),
+    # three and two blocks
+    (8, (140, 128, 129, 127, 112, 96, 150, 142), 1024, 1024, [(3, True), (3, True)], WIDE),
+    (4, (100, 97, 96, 112), 1984, 2044, [(3, True), (3, True)], WIDE),
+    (4, (256, 193, 240, 241), 1000, 1000, [(2, True), (2, True)], BLOCK),
+    (66, fill(66, (65, 64, 0, 33, 32), (60, 61)), 260, 260, [(2, False), (2, False)], WIDE),
+    # more than 64 experts are counted in pieces; few rows
+    (100, fill(100, (125, 0, 0, 96, 97), (100, 111, 64, 90)), 256, 256, [(5, False), (5, False)], WIDE),
+    (70, fill(70, (7, 0, 64, 65), (50, 49, 6)), 388, 324, [(5, False), (5, False)], WIDE),
+    # tokens far from even: tiles of fewer blocks, as long as each has a unit
+    (8, (700, 320, 6, 0, 7, 16, 17, 6), 1024, 1024, [(3, True), (3, True)], WIDE),
+    (8, (320, 0, 0, 0, 1100, 320, 0, 0), 512, 512, [(2, True), (2, True)], BLOCK),
+])
+def test_block_form(orc, E, rows, h, f, want, wgrad):
+    assert forms(E, rows, h, f) == (want, wgrad)
+    run_rows(orc, rows, h, f, dtype="f32")
+
+
+def test_estimates_never_ask_for_a_second_round_alone():
+    """A tile alone on its compute unit is only planned where an average layer has no more tiles than units."""
+    r = choice()
+    for E in (1, 2, 8, 64, 256):
+        for R in (1, 16, 100, 255, 256, 1000, 5000):
+            for N in (4, 64, 260, 1024, 8192):
+                for K in (4, 32, 1000, 4096):
+                    mb, lone = divmod(r.f32_plan(E, R, N, K), 2)
+                    assert mb in (0, 2, 3, 5)
+                    if lone:
+                        assert E * -(-N // 64) * -(-(R // 16 + 1) // (2 * mb)) <= 256
