@@ -81,7 +81,7 @@ __device__ __forceinline__ int tile_cost(int nblk) { return nblk >= 9 ? 19 : nbl
 struct PlanDesc {
     const int32_t *kept;
     int32_t *plan;
-    int E, M, K, nt, rows_from_kept, maxb, cus_per_xcd;
+    int E, M, K, nt, rows_from_kept, maxb, cus_per_xcd, low_tiles;
 };
 struct PlanArgs {
     PlanDesc p[MAX_PLANS];
@@ -94,17 +94,33 @@ __global__ __launch_bounds__(PLAN_THREADS) void gemm_plan_kernel(PlanArgs args) 
     __shared__ long long s_preW[257], s_w[256];   // work of the heavy tiles of the experts before e, and of expert e
     __shared__ long long s_w0[256];               // work by expert index, for the ordering
     __shared__ int s_ts[9], s_sl[9];              // split points of the heavy and of the light list
+    __shared__ int s_tiles[2];
     const int tid = threadIdx.x, nt = p.nt;
-    int kx = 0, nb = 0, nkf = 1;
+    int kx = 0, nb = 0, nkf = 1, maxb = p.maxb;
     long long w = 0;
     if (tid < p.E) {
         kx = p.kept[tid];
         const int Mx = p.rows_from_kept ? kx : p.M;
         nb = (Mx + 31) >> 5;
+    }
+    // Few tiles (the host counts them by capacity; with an uneven router most experts may hold next to nothing): tiles of at
+    // most LIGHT_BLOCKS blocks, twice as many and half as much MFMA work in each, if they fit one round and the plan.
+    // Forward pair, 64 experts of 2048 x 4096, nine with rows, three of them 256 (144 and 72 tiles, now 192 and 96): 147 -> 131 us.
+    if (p.low_tiles > 0) {
+        if (tid < 2) s_tiles[tid] = 0;
+        __syncthreads();
+        if (nb > 0) {
+            atomicAdd(&s_tiles[0], nb > LIGHT_BLOCKS ? (nb + maxb - 1) / maxb : 1);
+            atomicAdd(&s_tiles[1], (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS);
+        }
+        __syncthreads();
+        if (s_tiles[0] * nt <= 5 * p.cus_per_xcd && s_tiles[1] * nt <= p.low_tiles) maxb = LIGHT_BLOCKS;
+    }
+    if (tid < p.E) {
         const int nk = p.rows_from_kept ? 1 : (kx + BK - 1) / BK;
         nkf = nk > 0 ? nk : 1;                    // never 0: every heavy tile must fall into some share
         if (nb > LIGHT_BLOCKS) {  // one column of the expert's tiles: bx tiles of bb + 1 blocks, the others of bb
-            const int hv = (nb + p.maxb - 1) / p.maxb, bb = nb / hv, bx = nb - bb * hv;
+            const int hv = (nb + maxb - 1) / maxb, bb = nb / hv, bx = nb - bb * hv;
             w = (long long)(bx * tile_cost(bb + 1) + (hv - bx) * tile_cost(bb)) * nkf * nt;
         }
         s_w0[tid] = w;
@@ -121,7 +137,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void gemm_plan_kernel(PlanArgs args) 
         s_eid[pos] = tid;
         s_kept[pos] = kx;
         s_nb[pos] = nb;
-        s_hv[pos] = nb > LIGHT_BLOCKS ? (nb + p.maxb - 1) / p.maxb : 0;
+        s_hv[pos] = nb > LIGHT_BLOCKS ? (nb + maxb - 1) / maxb : 0;
         s_nk[pos] = nkf;
         s_w[pos] = w;
     }
@@ -746,6 +762,10 @@ moe_status_t launch_gemm_bf16_plans(const GemmDesc *descs, int n, hipStream_t s)
         p.E = d.E; p.M = d.M; p.K = d.K; p.nt = (d.N + BN - 1) / BN;
         p.rows_from_kept = d.rows_from_kept; p.maxb = d.a_xc ? 8 : MAXB;
         p.cus_per_xcd = num_compute_units() / 8 > 0 ? num_compute_units() / 8 : 1;
+        if (p.rows_from_kept) {
+            const int64_t room = (int64_t)p.E * ((p.M + BM - 1) / BM) * p.nt;          // tiles of the plan buffer
+            p.low_tiles = (int)(room < 8 * p.cus_per_xcd ? room : 8 * p.cus_per_xcd);
+        }
     }
     if (np == 0) return MOE_OK;
     hipLaunchKernelGGL(gemm_plan_kernel, dim3(np, PLAN_SLICES), dim3(PLAN_THREADS), 0, s, args);
