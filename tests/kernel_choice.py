@@ -63,19 +63,25 @@ class Rules:
         return ("rows", b, bool(self.gemm_rows_lone(self.gemm_rows_tiles(E, C, N, b), b, forward)))
 
     def weight_gemm(self, E, C, M, N, aligned=True):
-        """Kernel of a weight gradient [M, N] over C rows: 'large', or ('wgrad', whole lines, tiles of the longest and of
-        the last run).  aligned: the result array starts on a cache line."""
+        """Kernel of a weight gradient [M, N] over C rows where the panel kernel does not come first: 'large', or ('wgrad', whole
+        lines, tiles of the longest and of the last run).  aligned: the result array starts on a cache line."""
         whole = aligned and N % 64 == 0
         if not self.gemm_wgrad_chosen(E, M, N, C, whole):
             return "large"
         nt, run = -(-N // 128), self.gemm_wgrad_run(E, M, N)
         return ("wgrad", whole, min(run, nt), (nt - 1) % run + 1)
 
+    def gradient_gemm(self, E, C, M, N):
+        """Kernel of a weight gradient into an aligned array: ('panel', row tiles of a run), or as above"""
+        if N % 64 == 0 and self.gemm_panel_chosen(E, M, N, C):
+            return ("panel", self.gemm_panel_run(E, M, N, C))
+        return self.weight_gemm(E, C, M, N)
+
     def layer_gemms(self, E, C, h, f):
         """Kernels of a bf16 layer's GEMMs"""
         return {"fwd1": self.row_gemm(E, C, f, True), "fwd2": self.row_gemm(E, C, h, True),
                 "dh": self.row_gemm(E, C, f, False), "dd": self.row_gemm(E, C, h, False),
-                "dw2": self.weight_gemm(E, C, f, h), "dw1": self.weight_gemm(E, C, h, f)}
+                "dw2": self.gradient_gemm(E, C, f, h), "dw1": self.gradient_gemm(E, C, h, f)}
 
 
 def choice() -> Rules:

@@ -16,8 +16,8 @@ from test_gpu_gemm_kernels import spread
     (17, (160, 130, 0, 7), 1088, 2624),                                     # workgroups that do not divide by eight
 ])
 def test_panel_kernel(orc, E, rows, h, f):
-    r = choice()
-    assert r.gemm_panel_chosen(E, h, f, max(rows)) and r.gemm_panel_chosen(E, f, h, max(rows))
+    k = choice().layer_gemms(E, max(rows), h, f)
+    assert k["dw1"][0] == "panel" and k["dw2"][0] == "panel", k
     run_rows(orc, spread(E, rows) if max(rows) > 40 else rows + tuple(n % 32 for n in range(E - len(rows))), h, f, per_expert=True)
 
 
