@@ -88,22 +88,25 @@ __device__ __forceinline__ void gate_choose(const float (*lg)[EP + 1], int32_t *
 }
 
 // ------------------------------------------------------------------ fused gate, bf16 tokens, up to 64 experts
-// A workgroup of 4 waves takes 64 tokens; x and the planes of Wg go straight into LDS in k-tiles of 64 through a ring
-// of S stages (the loaders of the grouped GEMMs); a wave multiplies 16 NT tokens with one of the NT expert tiles.
-// Bound by latency: a k-tile is waited for S - 1 k-tiles after its request, 24 KB of x in flight per compute unit, and takes
-// 0.6 us (16384 tokens, h = 4096, E = 16: 64 k-tiles, 38 us) to 1.0 us (h = 2048, E = 64: 32 k-tiles, 33 us), about three
-// times what its bytes take from the L2 at 29 cycles per KB.  MFMA fragments loaded from memory directly are requests of 64
-// bytes out of 16 rows each, half a cache line.  Whole moe_gate call, 16384 tokens, with fragments from memory / now:
-// h = 4096, E = 16: 38.5 / 32.9 us; h = 2048, E = 64: 52.6 / 46.0.
+// A workgroup of 8 waves takes 64 tokens; x and the planes of Wg go straight into LDS in k-tiles of 64 through a ring
+// of S stages (the loaders of the grouped GEMMs); four waves take the first k-step of a k-tile and four the second, each
+// 16 NT tokens with one of the NT expert tiles.  Two waves per SIMD, so that one reads fragments while the other multiplies
+// (with four waves, both k-steps in each, LDS reads, MFMAs and the barrier follow each other).  Whole moe_gate call, us, with
+// four waves / eight, tokens after 1 GB of writes and in cache: 16384 x 2048, E = 64: 60.2 and 47.6 / 58.0 and 40.1;
+// 5000 x 4096, E = 64: 68.9 and 60.5 / 65.9 and 47.4; 65536 x 1024, E = 64: 122 and 106 / 115 and 87; 16384 x 2560, E = 32:
+// 55.0 and 36.0 / 54.6 and 33.3; 16384 x 4096, E = 16: 69.8 and 35.6 / 69.5 and 34.8 (those bytes' cold read and the two other
+// launches).  Not bound by what is in flight: a ring of 6 to 16 k-tiles of x costs 0 to 4 us.
+// MFMA fragments loaded from memory directly are requests of 64 bytes out of 16 rows each, half a cache line (h = 4096,
+// E = 16: 38.5 us for the call where the ring takes 32.9).
 // The sums of the high planes run in four chains (k-step parity x k-tile parity), those of the other planes in a
-// chain of their own, so that fewer roundings at the size of the result follow each other than with one chain.
+// chain per k-step, so that fewer roundings at the size of the result follow each other than with one chain.
 template <int NT, int S>
-__global__ __launch_bounds__(256) void gate_stream_kernel(const bf16_t *x, const bf16_t *planes, const float *bias,
+__global__ __launch_bounds__(512) void gate_stream_kernel(const bf16_t *x, const bf16_t *planes, const float *bias,
                                                           float *logits, float *probs, int32_t *expert, float *gate_p,
                                                           int64_t T, int h, int E, int32_t *hist, int32_t *token_of_slot,
                                                           int64_t EC) {
-    constexpr int EP = NT * 16, TM = 64, PQ = (6 * NT + 3) / 4, L = 2 + PQ;      // 1 KB requests of a wave per k-tile: 2 of x, PQ of the planes
-    constexpr int X_BYTES = TM * KC_ROW, STAGE = X_BYTES + PQ * 4096;
+    constexpr int EP = NT * 16, TM = 64, PQ = (6 * NT + 7) / 8, L = 1 + PQ;      // 1 KB requests of a wave per k-tile: 1 of x, PQ of the planes
+    constexpr int X_BYTES = TM * KC_ROW, STAGE = X_BYTES + PQ * 8192;
     static_assert(TM * (EP + 1) * 4 <= S * STAGE, "the logits are staged in the operand stages");
     __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
     __shared__ int32_t hist_s[EP];
@@ -113,29 +116,31 @@ __global__ __launch_bounds__(256) void gate_stream_kernel(const bf16_t *x, const
     const int rows = (int)(T - t0 < TM ? T - t0 : TM);
     const i32x4 X = make_rsrc(x + t0 * h, (uint32_t)rows * (uint32_t)h * 2u);
     const i32x4 P = make_rsrc(planes, (uint32_t)(3 * EP) * (uint32_t)h * 2u);
-    Loader<false, 2, 128, 4> lx;
-    Loader<false, PQ, 128, 4> lp;
+    Loader<false, 1, 128> lx;
+    Loader<false, PQ, 128> lp;
     lx.init(h, 0, rows, wave, lane);
     lp.init(h, 0, 3 * EP, wave, lane);
     lx.init_k(h, wave, lane);
     lp.kthr = lx.kthr;
     FragAddr<false, 128> fx, fp;
-    const int wn = wave % NT, wm = wave / NT * NT;               // the wave's expert tile and first 16-token block (of NT)
+    const int ks = wave >> 2, wn = (wave & 3) % NT, wm = (wave & 3) / NT * NT;   // the wave's k-step, expert tile and first 16-token block (of NT)
     fx.init(wm * 16, lane);
     fp.init(wn * 16, lane);
+    if (ks != 0) {
+        fx.a[0] = fx.a[1];
+        fp.a[0] = fp.a[1];
+    }
     auto request = [&](int kt, int stage) {                      // past the end of h: zeros, without memory traffic
         const uint32_t base = smem_addr + stage * STAGE + wave * 1024;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) lx.request(X, base, kt * BK, h, q);
+        lx.request(X, base, kt * BK, h, 0);
 #pragma unroll
         for (int q = 0; q < PQ; ++q) lp.request(P, base + X_BYTES, kt * BK, h, q);
     };
-    f32x4 hi[4][NT], low[NT];
+    f32x4 hi[2][NT], low[NT];
 #pragma unroll
     for (int r = 0; r < NT; ++r) {
         low[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) hi[c][r] = low[r];
+        hi[0][r] = hi[1][r] = low[r];
     }
     const int nk = (h + BK - 1) / BK;
 #pragma unroll
@@ -150,21 +155,20 @@ __global__ __launch_bounds__(256) void gate_stream_kernel(const bf16_t *x, const
         __builtin_amdgcn_sched_barrier(0);
         request(kt + S - 1, stage == 0 ? S - 1 : stage - 1);
         const char *tx = smem + stage * STAGE, *tp = tx + X_BYTES;
+        bf16x8 a[NT], b[3];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            bf16x8 a[NT], b[3];
+        for (int p = 0; p < 3; ++p) b[p] = fp.read(tp, p * NT, 0);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) b[p] = fp.read(tp, p * NT, ks);
+        for (int r = 0; r < NT; ++r) a[r] = fx.read(tx, r, 0);
 #pragma unroll
-            for (int r = 0; r < NT; ++r) a[r] = fx.read(tx, r, ks);
+        for (int r = 0; r < NT; ++r) low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[1], low[r], 0, 0, 0);
 #pragma unroll
-            for (int r = 0; r < NT; ++r) {
-                f32x4 &c = hi[2 * decltype(parity)::value + ks][r];
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[0], c, 0, 0, 0);
-                low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[1], low[r], 0, 0, 0);
-                low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[2], low[r], 0, 0, 0);
-            }
+        for (int r = 0; r < NT; ++r) {
+            f32x4 &c = hi[decltype(parity)::value][r];
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[0], c, 0, 0, 0);
         }
+#pragma unroll
+        for (int r = 0; r < NT; ++r) low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[2], low[r], 0, 0, 0);
         stage = stage == S - 1 ? 0 : stage + 1;
     };
     for (int kt = 0; kt < nk; kt += 2) {
@@ -174,22 +178,29 @@ __global__ __launch_bounds__(256) void gate_stream_kernel(const bf16_t *x, const
     __builtin_amdgcn_sched_barrier(0);
     wait_outstanding<0>();                          // nothing may still be writing LDS when it is reused
     __syncthreads();
-    // 16x16 result: lane holds column (expert) lane%16, rows (tokens) 4*(lane/16) + v
+    // 16x16 result: lane holds column (expert) lane%16, rows (tokens) 4*(lane/16) + v; the two k-steps add up here
     float(*lg)[EP + 1] = (float(*)[EP + 1])smem;
 #pragma unroll
-    for (int r = 0; r < NT; ++r)
+    for (int step = 0; step < 2; ++step) {
+        if (ks == step)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            lg[(wm + r) * 16 + (lane >> 4) * 4 + v][wn * 16 + (lane & 15)] = ((hi[0][r][v] + hi[1][r][v]) + (hi[2][r][v] + hi[3][r][v])) + low[r][v];
-    __syncthreads();
-    for (int idx = tid; idx < TM * E; idx += 256) {
+            for (int r = 0; r < NT; ++r)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    float &o = lg[(wm + r) * 16 + (lane >> 4) * 4 + v][wn * 16 + (lane & 15)];
+                    const float sum = (hi[0][r][v] + hi[1][r][v]) + low[r][v];
+                    o = step ? o + sum : sum;
+                }
+        __syncthreads();
+    }
+    for (int idx = tid; idx < TM * E; idx += 512) {
         const int tt = idx / E, j = idx - tt * E;
         float v = lg[tt][j];
         if (bias) v += bias[j];
         lg[tt][j] = v;
         if (t0 + tt < T) logits[(t0 + tt) * E + j] = v;
     }
-    gate_choose<EP, TM, 256>(lg, hist_s, probs, expert, gate_p, T, E, hist, token_of_slot, EC);
+    gate_choose<EP, TM, 512>(lg, hist_s, probs, expert, gate_p, T, E, hist, token_of_slot, EC);
 }
 
 // ------------------------------------------------------------------ fused gate, bf16 tokens, more experts
@@ -592,7 +603,7 @@ moe_status_t run_gate(const moe_shape_t *sh, const void *x, const float *w_gate,
         hipLaunchKernelGGL(gate_split_wg_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w_gate, planes,
                            sh->h, sh->E, NT * 16);
 #define MOE_GATE_STREAM(NT_, S_)                                                                                              \
-    hipLaunchKernelGGL((gate_stream_kernel<NT_, S_>), dim3((unsigned)((T + 63) / 64)), dim3(256), 0, s, (const bf16_t *)x, planes, \
+    hipLaunchKernelGGL((gate_stream_kernel<NT_, S_>), dim3((unsigned)((T + 63) / 64)), dim3(512), 0, s, (const bf16_t *)x, planes, \
                        bias, logits, probs, expert, gate_p, T, sh->h, sh->E, hist, token_of_slot, (int64_t)sh->E * sh->C)
         // launch_gate_bf16: 16-expert tiles, tokens per workgroup / 16, waves, k-steps per batch
         switch (NT) {
