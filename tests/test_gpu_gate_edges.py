@@ -23,6 +23,8 @@ SIZES = [
     (4161, 136, 24), (3100, 4096, 24), (6200, 4096, 24), (2600, 2056, 40), (5000, 2056, 40), (1040, 2056, 65),
     # few tokens of more than 64 experts: d_w_gate by the bf16 kernel
     (16, 72, 65), (33, 136, 256),
+    # the ring of four expert tiles: a last k-tile with a part of its second k-step, and one k-tile
+    (4150, 104, 64), (4100, 40, 33),
 ]
 
 
