@@ -107,14 +107,28 @@ __global__ __launch_bounds__(PLAN_THREADS) void gemm_plan_kernel(PlanArgs args) 
     // most LIGHT_BLOCKS blocks, twice as many and half as much MFMA work in each, if they fit one round and the plan.
     // Forward pair, 64 experts of 2048 x 4096, nine with rows, three of them 256 (144 and 72 tiles, now 192 and 96): 147 -> 131 us.
     if (p.low_tiles > 0) {
-        if (tid < 2) s_tiles[tid] = 0;
-        __syncthreads();
-        if (nb > 0) {
-            atomicAdd(&s_tiles[0], nb > LIGHT_BLOCKS ? (nb + maxb - 1) / maxb : 1);
-            atomicAdd(&s_tiles[1], (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS);
+        const int tall = nb > LIGHT_BLOCKS ? (nb + maxb - 1) / maxb : nb > 0, low = (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS;
+        int tall_sum = 0, low_sum = 0;
+        // Up to 64 experts are in one wave, which adds up bit by bit (1023 tiles never fit): without the barriers and atomics the
+        // plan of 16 experts takes 7.7 us for 9.3 (2048 x 8192) and 6.9 for 7.8 (one round of tiles).
+        if (p.E <= 64) {
+#pragma unroll
+            for (int b = 0; b < 10; ++b) {
+                tall_sum += __popcll(__ballot(((tall < 1023 ? tall : 1023) >> b) & 1)) << b;
+                low_sum += __popcll(__ballot(((low < 1023 ? low : 1023) >> b) & 1)) << b;
+            }
+        } else {
+            if (tid < 2) s_tiles[tid] = 0;
+            __syncthreads();
+            if (nb > 0) {
+                atomicAdd(&s_tiles[0], tall);
+                atomicAdd(&s_tiles[1], low);
+            }
+            __syncthreads();
+            tall_sum = s_tiles[0];
+            low_sum = s_tiles[1];
         }
-        __syncthreads();
-        if (s_tiles[0] * nt <= 5 * p.cus_per_xcd && s_tiles[1] * nt <= p.low_tiles) maxb = LIGHT_BLOCKS;
+        if (tall_sum * nt <= 5 * p.cus_per_xcd && low_sum * nt <= p.low_tiles) maxb = LIGHT_BLOCKS;
     }
     if (tid < p.E) {
         const int nk = p.rows_from_kept ? 1 : (kx + BK - 1) / BK;
