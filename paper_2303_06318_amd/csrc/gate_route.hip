@@ -37,8 +37,9 @@ __global__ void gate_split_wg_kernel(const float *wg, bf16_t *planes, int h, int
 }
 
 // ------------------------------------------------------------------ choice of the expert, from the logits in LDS
-// (all threads of the workgroup of TM tokens; the logits are complete before the call)
-template <int EP, int TM, int THREADS>
+// (all threads of the workgroup of TM tokens; the logits are complete before the call; TPT lanes per token, whose sums
+// fix the last bits of the probabilities)
+template <int EP, int TM, int THREADS, int TPT = THREADS / TM>
 __device__ __forceinline__ void gate_choose(const float (*lg)[EP + 1], int32_t *hist_s, float *probs, int32_t *expert,
                                             float *gate_p, int64_t T, int E, int32_t *hist, int32_t *token_of_slot,
                                             int64_t EC) {
@@ -49,9 +50,9 @@ __device__ __forceinline__ void gate_choose(const float (*lg)[EP + 1], int32_t *
     // Softmax and top-1 with TPT adjacent lanes per token: lane `sub` looks at experts sub, sub + TPT, ...;
     // the lanes' candidates are merged by butterfly exchanges (larger logit wins, the lower index among
     // equal ones: the same choice as a left-to-right scan with a strict comparison).
-    constexpr int TPT = THREADS / TM;
-    static_assert(TPT >= 1 && (TPT & (TPT - 1)) == 0 && TPT <= 64, "lanes per token");
-    const int tt = tid / TPT, sub = tid % TPT;
+    static_assert(TPT >= 1 && (TPT & (TPT - 1)) == 0 && TPT <= 64 && TM * TPT <= THREADS && (TM * TPT == THREADS || TM * TPT % 64 == 0),
+                  "lanes per token, in whole waves");
+    const int tt = tid / TPT, sub = TM * TPT == THREADS || tt < TM ? tid % TPT : E;      // waves without tokens look at no expert
     const float *row = &lg[tt][0];
     float best = -__builtin_inff();
     int bi = 0x7fffffff;
@@ -88,25 +89,29 @@ __device__ __forceinline__ void gate_choose(const float (*lg)[EP + 1], int32_t *
 }
 
 // ------------------------------------------------------------------ fused gate, bf16 tokens, up to 64 experts
-// A workgroup of 8 waves takes 64 tokens; x and the planes of Wg go straight into LDS in k-tiles of 64 through a ring
-// of S stages (the loaders of the grouped GEMMs); four waves take the first k-step of a k-tile and four the second, each
-// 16 NT tokens with one of the NT expert tiles.  Two waves per SIMD, so that one reads fragments while the other multiplies
-// (with four waves, both k-steps in each, LDS reads, MFMAs and the barrier follow each other).  Whole moe_gate call, us, with
-// four waves / eight, tokens after 1 GB of writes and in cache: 16384 x 2048, E = 64: 60.2 and 47.6 / 58.0 and 40.1;
-// 5000 x 4096, E = 64: 68.9 and 60.5 / 65.9 and 47.4; 65536 x 1024, E = 64: 122 and 106 / 115 and 87; 16384 x 2560, E = 32:
-// 55.0 and 36.0 / 54.6 and 33.3; 16384 x 4096, E = 16: 69.8 and 35.6 / 69.5 and 34.8 (those bytes' cold read and the two other
-// launches).  Not bound by what is in flight: a ring of 6 to 16 k-tiles of x costs 0 to 4 us.
+// A workgroup of W waves takes 64 tokens; x and the planes of Wg go straight into LDS in k-tiles of 64 through a ring
+// of S stages (the loaders of the grouped GEMMs); a wave multiplies RW blocks of 16 tokens with one of the NT expert tiles.
+// From two expert tiles on there are eight waves, two per SIMD, so that one reads fragments while the other multiplies (with
+// four, LDS reads, MFMAs and the barrier follow each other).  Whole moe_gate call, us, four waves / eight, tokens after 1 GB of
+// writes and in cache: 16384 x 2048, E = 64: 59.9 and 48.8 / 58.7 and 42.4; 5000 x 4096, E = 64: 68.8 and 61.6 / 66.4 and 49.5;
+// 65536 x 1024, E = 64: 122 and 107 / 115 and 90; 16384 x 2560, E = 32: 55.0 and 37.0 / 54.8 and 35.2.  Not bound by what is in
+// flight: a ring of 6 to 16 k-tiles of x costs 0 to 4 us.  One expert tile is four blocks, one for each of four waves:
+// 16384 x 4096, E = 16: 69.4 and 35.5.
 // MFMA fragments loaded from memory directly are requests of 64 bytes out of 16 rows each, half a cache line (h = 4096,
 // E = 16: 38.5 us for the call where the ring takes 32.9).
 // The sums of the high planes run in four chains (k-step parity x k-tile parity), those of the other planes in a
-// chain per k-step, so that fewer roundings at the size of the result follow each other than with one chain.
-template <int NT, int S>
-__global__ __launch_bounds__(512) void gate_stream_kernel(const bf16_t *x, const bf16_t *planes, const float *bias,
-                                                          float *logits, float *probs, int32_t *expert, float *gate_p,
-                                                          int64_t T, int h, int E, int32_t *hist, int32_t *token_of_slot,
-                                                          int64_t EC) {
-    constexpr int EP = NT * 16, TM = 64, PQ = (6 * NT + 7) / 8, L = 1 + PQ;      // 1 KB requests of a wave per k-tile: 1 of x, PQ of the planes
-    constexpr int X_BYTES = TM * KC_ROW, STAGE = X_BYTES + PQ * 8192;
+// chain of their own that is added last, so that fewer roundings at the size of the result follow each other than with one
+// chain.  (Eight waves of which four take either k-step read a third fewer fragments and take 1 to 3 us less with 64 experts,
+// but each then adds its low sum to its half of the high one: one more rounding, error against 64 bits at h = 40 4.5e-8 for 4.2e-8.)
+template <int NT, int S, int W>
+__global__ __launch_bounds__(64 * W) void gate_stream_kernel(const bf16_t *x, const bf16_t *planes, const float *bias,
+                                                             float *logits, float *probs, int32_t *expert, float *gate_p,
+                                                             int64_t T, int h, int E, int32_t *hist, int32_t *token_of_slot,
+                                                             int64_t EC) {
+    constexpr int EP = NT * 16, TM = 64, RW = 4 * NT / W;                        // a wave's blocks of 16 tokens
+    constexpr int XQ = 8 / W, PQ = (6 * NT + W - 1) / W, L = XQ + PQ;            // 1 KB requests of a wave per k-tile: of x, of the planes
+    constexpr int X_BYTES = TM * KC_ROW, STAGE = X_BYTES + PQ * W * 1024;
+    static_assert(RW >= 1, "every wave has a block");
     static_assert(TM * (EP + 1) * 4 <= S * STAGE, "the logits are staged in the operand stages");
     __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
     __shared__ int32_t hist_s[EP];
@@ -116,31 +121,29 @@ __global__ __launch_bounds__(512) void gate_stream_kernel(const bf16_t *x, const
     const int rows = (int)(T - t0 < TM ? T - t0 : TM);
     const i32x4 X = make_rsrc(x + t0 * h, (uint32_t)rows * (uint32_t)h * 2u);
     const i32x4 P = make_rsrc(planes, (uint32_t)(3 * EP) * (uint32_t)h * 2u);
-    Loader<false, 1, 128> lx;
-    Loader<false, PQ, 128> lp;
+    Loader<false, XQ, 128, W> lx;
+    Loader<false, PQ, 128, W> lp;
     lx.init(h, 0, rows, wave, lane);
     lp.init(h, 0, 3 * EP, wave, lane);
     lx.init_k(h, wave, lane);
     lp.kthr = lx.kthr;
     FragAddr<false, 128> fx, fp;
-    const int ks = wave >> 2, wn = (wave & 3) % NT, wm = (wave & 3) / NT * NT;   // the wave's k-step, expert tile and first 16-token block (of NT)
+    const int wn = wave % NT, wm = wave / NT * RW;               // the wave's expert tile and first block of 16 tokens (of RW)
     fx.init(wm * 16, lane);
     fp.init(wn * 16, lane);
-    if (ks != 0) {
-        fx.a[0] = fx.a[1];
-        fp.a[0] = fp.a[1];
-    }
     auto request = [&](int kt, int stage) {                      // past the end of h: zeros, without memory traffic
         const uint32_t base = smem_addr + stage * STAGE + wave * 1024;
-        lx.request(X, base, kt * BK, h, 0);
+#pragma unroll
+        for (int q = 0; q < XQ; ++q) lx.request(X, base, kt * BK, h, q);
 #pragma unroll
         for (int q = 0; q < PQ; ++q) lp.request(P, base + X_BYTES, kt * BK, h, q);
     };
-    f32x4 hi[2][NT], low[NT];
+    f32x4 hi[4][RW], low[RW];
 #pragma unroll
-    for (int r = 0; r < NT; ++r) {
+    for (int r = 0; r < RW; ++r) {
         low[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-        hi[0][r] = hi[1][r] = low[r];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) hi[c][r] = low[r];
     }
     const int nk = (h + BK - 1) / BK;
 #pragma unroll
@@ -155,20 +158,26 @@ __global__ __launch_bounds__(512) void gate_stream_kernel(const bf16_t *x, const
         __builtin_amdgcn_sched_barrier(0);
         request(kt + S - 1, stage == 0 ? S - 1 : stage - 1);
         const char *tx = smem + stage * STAGE, *tp = tx + X_BYTES;
-        bf16x8 a[NT], b[3];
+        bf16x8 a[KS][RW], b[KS][3];
 #pragma unroll
-        for (int p = 0; p < 3; ++p) b[p] = fp.read(tp, p * NT, 0);
+        for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-        for (int r = 0; r < NT; ++r) a[r] = fx.read(tx, r, 0);
+            for (int p = 0; p < 3; ++p) b[ks][p] = fp.read(tp, p * NT, ks);
 #pragma unroll
-        for (int r = 0; r < NT; ++r) low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[1], low[r], 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < NT; ++r) {
-            f32x4 &c = hi[decltype(parity)::value][r];
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[0], c, 0, 0, 0);
+            for (int r = 0; r < RW; ++r) a[ks][r] = fx.read(tx, r, ks);
         }
 #pragma unroll
-        for (int r = 0; r < NT; ++r) low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b[2], low[r], 0, 0, 0);
+        for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r) low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][r], b[ks][1], low[r], 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                f32x4 &c = hi[2 * decltype(parity)::value + ks][r];
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][r], b[ks][0], c, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < RW; ++r) low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][r], b[ks][2], low[r], 0, 0, 0);
+        }
         stage = stage == S - 1 ? 0 : stage + 1;
     };
     for (int kt = 0; kt < nk; kt += 2) {
@@ -178,29 +187,22 @@ __global__ __launch_bounds__(512) void gate_stream_kernel(const bf16_t *x, const
     __builtin_amdgcn_sched_barrier(0);
     wait_outstanding<0>();                          // nothing may still be writing LDS when it is reused
     __syncthreads();
-    // 16x16 result: lane holds column (expert) lane%16, rows (tokens) 4*(lane/16) + v; the two k-steps add up here
+    // 16x16 result: lane holds column (expert) lane%16, rows (tokens) 4*(lane/16) + v
     float(*lg)[EP + 1] = (float(*)[EP + 1])smem;
 #pragma unroll
-    for (int step = 0; step < 2; ++step) {
-        if (ks == step)
+    for (int r = 0; r < RW; ++r)
 #pragma unroll
-            for (int r = 0; r < NT; ++r)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    float &o = lg[(wm + r) * 16 + (lane >> 4) * 4 + v][wn * 16 + (lane & 15)];
-                    const float sum = (hi[0][r][v] + hi[1][r][v]) + low[r][v];
-                    o = step ? o + sum : sum;
-                }
-        __syncthreads();
-    }
-    for (int idx = tid; idx < TM * E; idx += 512) {
+        for (int v = 0; v < 4; ++v)
+            lg[(wm + r) * 16 + (lane >> 4) * 4 + v][wn * 16 + (lane & 15)] = ((hi[0][r][v] + hi[1][r][v]) + (hi[2][r][v] + hi[3][r][v])) + low[r][v];
+    __syncthreads();
+    for (int idx = tid; idx < TM * E; idx += 64 * W) {
         const int tt = idx / E, j = idx - tt * E;
         float v = lg[tt][j];
         if (bias) v += bias[j];
         lg[tt][j] = v;
         if (t0 + tt < T) logits[(t0 + tt) * E + j] = v;
     }
-    gate_choose<EP, TM, 512>(lg, hist_s, probs, expert, gate_p, T, E, hist, token_of_slot, EC);
+    gate_choose<EP, TM, 64 * W, 4>(lg, hist_s, probs, expert, gate_p, T, E, hist, token_of_slot, EC);
 }
 
 // ------------------------------------------------------------------ fused gate, bf16 tokens, more experts
@@ -602,14 +604,14 @@ moe_status_t run_gate(const moe_shape_t *sh, const void *x, const float *w_gate,
         const int64_t n = (int64_t)NT * 16 * sh->h;
         hipLaunchKernelGGL(gate_split_wg_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w_gate, planes,
                            sh->h, sh->E, NT * 16);
-#define MOE_GATE_STREAM(NT_, S_)                                                                                              \
-    hipLaunchKernelGGL((gate_stream_kernel<NT_, S_>), dim3((unsigned)((T + 63) / 64)), dim3(512), 0, s, (const bf16_t *)x, planes, \
+#define MOE_GATE_STREAM(NT_, S_, W_)                                                                                          \
+    hipLaunchKernelGGL((gate_stream_kernel<NT_, S_, W_>), dim3((unsigned)((T + 63) / 64)), dim3(64 * W_), 0, s, (const bf16_t *)x, planes, \
                        bias, logits, probs, expert, gate_p, T, sh->h, sh->E, hist, token_of_slot, (int64_t)sh->E * sh->C)
         // launch_gate_bf16: 16-expert tiles, tokens per workgroup / 16, waves, k-steps per batch
         switch (NT) {
-            case 1: MOE_GATE_STREAM(1, 4); break;
-            case 2: MOE_GATE_STREAM(2, 4); break;
-            case 4: MOE_GATE_STREAM(4, 4); break;
+            case 1: MOE_GATE_STREAM(1, 4, 4); break;
+            case 2: MOE_GATE_STREAM(2, 4, 8); break;
+            case 4: MOE_GATE_STREAM(4, 4, 8); break;
             case 8: launch_gate_bf16<8, 1, 4, 1>(sh, x, planes, bias, logits, probs, expert, gate_p, hist, token_of_slot, s); break;
             default: launch_gate_bf16<16, 1, 4, 1>(sh, x, planes, bias, logits, probs, expert, gate_p, hist, token_of_slot, s); break;
         }

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2303_06318_amd import moe, synth
+from paper_2303_06318_amd.layer import MoeLayer
 from gpu_util import DevInputs, host, make_layer, relfro, tol
 from kernel_choice import choice
 
@@ -65,3 +66,22 @@ def test_sizes_reach_every_gate_kernel():
     rows = {(E > 32, r.gate_dx_chunk(T, h, E)) for T, h, E in SIZES if E <= 64 and not r.gate_dx_direct(False, T, h, E, True)}
     assert rows >= {(False, 48), (False, 96), (False, 192), (True, 48), (True, 96), (True, 192)}, rows
     assert {r.gate_dx_direct(False, T, h, E, False) for T, h, E in SIZES if E > 64} == {True, False}
+
+
+@pytest.mark.parametrize("h", [40, 136])
+@pytest.mark.parametrize("E", [3, 24, 64])
+def test_low_planes_are_added_to_the_whole_sum_of_the_high_plane(h, E):
+    """Long bf16 token tensors: Wg's high parts cancel between two 32-deep k-steps and a lower part, 2^-24 of either step's
+    sum, remains.  The order of the sums keeps it: it is added last, to the sum over all k-steps (2 + 2^-23 - 2 in fp32, step
+    after step, would give 0).  Every product and every sum in that order is exact, so the result is."""
+    T = 4100
+    assert not choice().gate_direct(False, T)
+    scale = 2.0 ** (torch.arange(T) % 5)
+    x = torch.zeros(T, h)
+    x[:, 0] = x[:, 1] = x[:, 32] = scale
+    wg = torch.zeros(h, E)
+    wg[0], wg[1], wg[32] = 1 + 2.0 ** -23, 1, -2
+    layer = MoeLayer(T, h, E, 8, T, moe.MOE_BF16)
+    layer.gate(x.bfloat16().cuda(), wg.cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(host(layer.logits), np.repeat((scale * 2.0 ** -23).numpy()[:, None], E, axis=1))
