@@ -1,7 +1,7 @@
 // Grouped fp32 GEMM for the fp32 storage type on the fp32 matrix instructions (fp32 products and fp32 sums, no
 // reduced-precision inputs; twice the rate of vector FMAs).  Three forms:
 //   block:  up to 32 MB rows (MB = 5, 3, 2) x 64 columns per workgroup of 8 waves, operands straight into LDS;
-//   wide:   64 x 64, 4 waves, each one 32 x 32 quarter, k-tiles of 32, two LDS stages (weight gradients only);
+//   wide:   64 x 64, 4 waves, each one 32 x 32 quarter, k-tiles of 32, two LDS stages (weight gradients, and the largest capacities);
 //   narrow: 32 x 32, 4 waves, k-tiles of 128 of which each wave takes 32, partial sums added through LDS at the end.
 // In the latter two global data goes through registers (the loads of the next k-tile are in flight during the MFMAs of the
 // current one).  Small tiles are bound by the path from L2 into the compute units: 8 experts x 256 rows of 1024 x 1024 in
@@ -390,11 +390,11 @@ static void launch_f32(const GemmDesc &d, hipStream_t s) {
             default: return launch_f32_tiles<EPI, AXC, BXC, false>(d, s);
         }
     } else {
-        F32Plan p = f32_plan(d.E, d.rows, d.N, d.K);
-        if ((int64_t)d.E * ((d.N + FB_N - 1) / FB_N) * ((d.M + 63) / 64) >= F32_MOST_TILES) p.mb = 0;
+        const F32Plan p = f32_row_plan(d.E, d.M, d.rows, d.N, d.K);
         if (p.mb == 5) launch_f32_block<EPI, AXC, BXC, 5>(d, s, p.lone);
         else if (p.mb == 3) launch_f32_block<EPI, AXC, BXC, 3>(d, s, p.lone);
         else if (p.mb == 2) launch_f32_block<EPI, AXC, BXC, 2>(d, s, p.lone);
+        else if (p.wide) launch_f32_tiles<EPI, AXC, BXC, true>(d, s);
         else launch_f32_tiles<EPI, AXC, BXC, false>(d, s);
     }
 }

@@ -3,7 +3,9 @@ the CPU oracle; tolerance as for every fp32 parity test (1e-5 per row and tile).
 is a sum over the expert's rows of hact times d_y, and where a single hact is next to zero (its z is a sum of 512 products with a
 rounding error of 1e-7, whatever computes it) that row's own norm measures nothing."""
 import pytest
+import torch
 
+from paper_2303_06318_amd import moe
 from kernel_choice import choice
 from test_gpu_gemm_edges import run_rows
 
@@ -54,3 +56,47 @@ def test_estimates_never_ask_for_a_second_round_alone():
                     assert mb in (0, 2, 3, 5)
                     if lone:
                         assert E * -(-N // 64) * -(-(R // 16 + 1) // (2 * mb)) <= 256
+
+
+def row_form(E, M, R, N, K):
+    v = choice().f32_row_plan(E, M, R, N, K)
+    return "block" if v >> 2 else "wide" if v & 2 else "narrow"
+
+
+def test_every_capacity_has_a_launch():
+    """Whatever an expert holds on average and may hold at most, the form that is chosen has a grid for it: fewer than 2^32 threads,
+    and at most 65535 workgroups in the second dimension (64-row tiles; beyond 4,194,240 rows only the block form, whose grid has one
+    dimension, has one)."""
+    for E in (1, 2, 8, 128, 256):
+        for M in (1, 2097120, 2097121, 2200000, 3000000, 4194240):
+            for R in (1, 50, 1000, M):
+                for N, K in ((4, 4), (64, 64), (128, 64), (64, 128)):
+                    form, tiles = row_form(E, M, min(R, M), N, K), E * -(-N // 64) * -(-M // 64)
+                    if form == "narrow":
+                        assert -(-M // 32) <= 65535, (E, M, R, N, K)
+                    elif form == "wide":
+                        assert -(-M // 64) <= 65535
+                    else:
+                        assert tiles < 1 << 22
+    assert row_form(128, 2200000, 2200000, 64, 64) == "wide" and row_form(1, 3000000, 100, 64, 64) == "wide"
+    assert row_form(1, 2097120, 100, 64, 64) == "narrow" and row_form(1, 2097121, 100, 64, 64) == "wide"
+
+
+@pytest.mark.gpu
+def test_wide_rows_beyond_the_grid_of_narrow_ones():
+    """A capacity that only the wide form's grid covers: the first rows of an expert with few, and every row of one that is full,
+    against the same pass in 64 bits; a relative error per row of 1e-5 as for every fp32 test."""
+    E, C, h, f = 2, 2097120 + 33, 8, 12
+    shape = moe.make_shape(200, h, E, f, C, moe.MOE_F32)
+    assert row_form(E, C, 100, f, h) == row_form(E, C, 100, h, f) == "wide"
+    g = torch.Generator(device="cuda").manual_seed(4)
+    buf, w1, w2 = (torch.randn(s, generator=g, device="cuda") for s in ((E, C, h), (E, h, f), (E, f, h)))
+    kept = torch.tensor([37, C], dtype=torch.int32, device="cuda")
+    hact, y = torch.full((E, C, f), float("nan"), device="cuda"), torch.full((E, C, h), float("nan"), device="cuda")
+    ws = torch.empty(moe.moe_workspace_bytes(shape, 0), dtype=torch.uint8, device="cuda")
+    moe.moe_expert_ffn_fwd(shape, buf, w1, w2, kept, None, hact, y, ws)
+    for e, k in enumerate((37, C)):
+        ref = torch.nn.functional.gelu(buf[e, :k].double() @ w1[e].double())
+        for got, want in ((hact[e, :k], ref), (y[e, :k], ref @ w2[e].double())):
+            assert bool(((got - want).norm(dim=1) <= 1e-5 * want.norm(dim=1).clamp_min(1e-3)).all())
+    assert bool(y[0, 37:].isnan().all())
