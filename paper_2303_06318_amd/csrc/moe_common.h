@@ -65,7 +65,6 @@ struct GemmDesc {
     const int32_t *kept;
     int64_t strideA, strideB, strideC;   // elements between experts
     int32_t M, N, K;                     // upper bounds / fixed sizes
-    int32_t rows;                        // what an expert holds when the tokens spread evenly, for the choice of a kernel only
     int32_t lda, ldb, ldc;
     int32_t E;
     int32_t a_xc, b_xc, rows_from_kept, epi, act;
@@ -84,6 +83,10 @@ struct GemmDesc {
     const int32_t *c_index;
     const float *c_scale;
     void *C_scatter;
+    // What an expert holds when the tokens spread evenly, for the choice of a kernel only.  Last, behind all that the bf16
+    // kernels read: between N and lda it changed how they load their arguments (4 experts, 4544 x 1472, 128 rows, forward
+    // layer 92.4 us, here 90.6).
+    int32_t rows;
 };
 
 moe_status_t launch_gemm_f32(const GemmDesc &d, hipStream_t s);
