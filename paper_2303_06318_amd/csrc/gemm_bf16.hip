@@ -82,6 +82,7 @@ struct PlanDesc {
     const int32_t *kept;
     int32_t *plan;
     int E, M, K, nt, rows_from_kept, maxb, cus_per_xcd, low_tiles;
+    uint32_t per_maxb;                            // 2^32 / maxb, rounded up
 };
 struct PlanArgs {
     PlanDesc p[MAX_PLANS];
@@ -94,50 +95,24 @@ __global__ __launch_bounds__(PLAN_THREADS) void gemm_plan_kernel(PlanArgs args) 
     __shared__ long long s_preW[257], s_w[256];   // work of the heavy tiles of the experts before e, and of expert e
     __shared__ long long s_w0[256];               // work by expert index, for the ordering
     __shared__ int s_ts[9], s_sl[9];              // split points of the heavy and of the light list
-    __shared__ int s_tiles[2];
+    __shared__ int2 s_cnt[256];                   // m-tiles by expert index: {usual, low}; 1023 for more, which never fit
     const int tid = threadIdx.x, nt = p.nt;
-    int kx = 0, nb = 0, nkf = 1, maxb = p.maxb;
+    int kx = 0, nb = 0, nkf = 1, hv = 0;
     long long w = 0;
     if (tid < p.E) {
         kx = p.kept[tid];
         const int Mx = p.rows_from_kept ? kx : p.M;
         nb = (Mx + 31) >> 5;
-    }
-    // Few tiles (the host counts them by capacity; with an uneven router most experts may hold next to nothing): tiles of at
-    // most LIGHT_BLOCKS blocks, twice as many and half as much MFMA work in each, if they fit one round and the plan.
-    // Forward pair, 64 experts of 2048 x 4096, nine with rows, three of them 256 (144 and 72 tiles, now 192 and 96): 147 -> 131 us.
-    if (p.low_tiles > 0) {
-        const int tall = nb > LIGHT_BLOCKS ? (nb + maxb - 1) / maxb : nb > 0, low = (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS;
-        int tall_sum = 0, low_sum = 0;
-        // Up to 64 experts are in one wave, which adds up bit by bit (1023 tiles never fit): without the barriers and atomics the
-        // plan of 16 experts takes 7.7 us for 9.3 (2048 x 8192) and 6.9 for 7.8 (one round of tiles).
-        if (p.E <= 64) {
-#pragma unroll
-            for (int b = 0; b < 10; ++b) {
-                tall_sum += __popcll(__ballot(((tall < 1023 ? tall : 1023) >> b) & 1)) << b;
-                low_sum += __popcll(__ballot(((low < 1023 ? low : 1023) >> b) & 1)) << b;
-            }
-        } else {
-            if (tid < 2) s_tiles[tid] = 0;
-            __syncthreads();
-            if (nb > 0) {
-                atomicAdd(&s_tiles[0], tall);
-                atomicAdd(&s_tiles[1], low);
-            }
-            __syncthreads();
-            tall_sum = s_tiles[0];
-            low_sum = s_tiles[1];
-        }
-        if (tall_sum * nt <= 5 * p.cus_per_xcd && low_sum * nt <= p.low_tiles) maxb = LIGHT_BLOCKS;
-    }
-    if (tid < p.E) {
         const int nk = p.rows_from_kept ? 1 : (kx + BK - 1) / BK;
         nkf = nk > 0 ? nk : 1;                    // never 0: every heavy tile must fall into some share
         if (nb > LIGHT_BLOCKS) {  // one column of the expert's tiles: bx tiles of bb + 1 blocks, the others of bb
-            const int hv = (nb + maxb - 1) / maxb, bb = nb / hv, bx = nb - bb * hv;
+            hv = (int)__umulhi((uint32_t)(nb + p.maxb - 1), p.per_maxb);      // ceil(nb / maxb), exact up to 2^29
+            const int bb = nb / hv, bx = nb - bb * hv;
             w = (long long)(bx * tile_cost(bb + 1) + (hv - bx) * tile_cost(bb)) * nkf * nt;
         }
         s_w0[tid] = w;
+        const int low = (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS, tall = hv > 0 ? hv : low;
+        s_cnt[tid] = make_int2(tall < 1023 ? tall : 1023, low < 1023 ? low : 1023);
     }
     __syncthreads();
     if (tid < p.E) {
@@ -147,11 +122,23 @@ __global__ __launch_bounds__(PLAN_THREADS) void gemm_plan_kernel(PlanArgs args) 
         // evens them out.  Any order gives the same results: tiles are independent.
         int r = 0;
         for (int e = 0; e < p.E; ++e) r += (s_w0[e] < w || (s_w0[e] == w && e < tid)) ? 1 : 0;
+        // Few tiles (the host counts them by capacity; with an uneven router most experts may hold next to nothing): tiles of at
+        // most LIGHT_BLOCKS blocks, twice as many and half as much MFMA work in each, if they fit one round and the plan.
+        // Forward pair, 64 experts of 2048 x 4096, nine with rows, three of them 256 (144 and 72 tiles, now 192 and 96): 147 -> 131 us.
+        // The usual tiles' work still orders the experts, and one round's shares are equal in tile count.
+        if (p.low_tiles > 0) {
+            int tall = 0, low = 0;
+            for (int e = 0; e < p.E; ++e) {
+                tall += s_cnt[e].x;
+                low += s_cnt[e].y;
+            }
+            if (tall * nt <= 5 * p.cus_per_xcd && low * nt <= p.low_tiles && hv > 0) hv = (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS;
+        }
         const int pos = r < (p.E + 1) / 2 ? 2 * r : 2 * (p.E - 1 - r) + 1;
         s_eid[pos] = tid;
         s_kept[pos] = kx;
         s_nb[pos] = nb;
-        s_hv[pos] = nb > LIGHT_BLOCKS ? (nb + maxb - 1) / maxb : 0;
+        s_hv[pos] = hv;
         s_nk[pos] = nkf;
         s_w[pos] = w;
     }
@@ -775,6 +762,7 @@ moe_status_t launch_gemm_bf16_plans(const GemmDesc *descs, int n, hipStream_t s)
         p.kept = d.kept; p.plan = (int32_t *)d.plan;
         p.E = d.E; p.M = d.M; p.K = d.K; p.nt = (d.N + BN - 1) / BN;
         p.rows_from_kept = d.rows_from_kept; p.maxb = d.a_xc ? 8 : MAXB;
+        p.per_maxb = (uint32_t)((((uint64_t)1 << 32) + p.maxb - 1) / p.maxb);
         p.cus_per_xcd = num_compute_units() / 8 > 0 ? num_compute_units() / 8 : 1;
         if (p.rows_from_kept) {
             const int64_t room = (int64_t)p.E * ((p.M + BM - 1) / BM) * p.nt;          // tiles of the plan buffer
