@@ -32,6 +32,7 @@
 // Rows beyond kept[e] are never read (loaded as zero) and never written.
 #include <type_traits>
 #include "gemm_bf16_parts.h"
+#include "kernel_choice.h"
 
 namespace moe {
 
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void gemm_plan_kernel(PlanArgs args) 
     __shared__ long long s_preW[257], s_w[256];   // work of the heavy tiles of the experts before e, and of expert e
     __shared__ long long s_w0[256];               // work by expert index, for the ordering
     __shared__ int s_ts[9], s_sl[9];              // split points of the heavy and of the light list
-    __shared__ int2 s_cnt[256];                   // m-tiles by expert index: {usual, low}; 1023 for more, which never fit
+    __shared__ int2 s_cnt[256];                   // m-tiles by expert index: {usual, low | light << 20}; 1023 for more, which never fit
     const int tid = threadIdx.x, nt = p.nt;
     int kx = 0, nb = 0, nkf = 1, hv = 0;
     long long w = 0;
@@ -111,8 +112,8 @@ __global__ __launch_bounds__(PLAN_THREADS) void gemm_plan_kernel(PlanArgs args) 
             w = (long long)(bx * tile_cost(bb + 1) + (hv - bx) * tile_cost(bb)) * nkf * nt;
         }
         s_w0[tid] = w;
-        const int low = (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS, tall = hv > 0 ? hv : low;
-        s_cnt[tid] = make_int2(tall < 1023 ? tall : 1023, low < 1023 ? low : 1023);
+        const int low = (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS;
+        s_cnt[tid] = hv > 0 ? make_int2(hv < 1023 ? hv : 1023, low < 1023 ? low : 1023) : make_int2(low, low << 20);
     }
     __syncthreads();
     if (tid < p.E) {
@@ -120,20 +121,17 @@ __global__ __launch_bounds__(PLAN_THREADS) void gemm_plan_kernel(PlanArgs args) 
         // mostly holds whole experts (their tiles share weight panels), and with few experts per share the
         // shares of a plain 0, 1, 2, ... order differ by the spread of the experts' sizes; pairing the extremes
         // evens them out.  Any order gives the same results: tiles are independent.
-        int r = 0;
-        for (int e = 0; e < p.E; ++e) r += (s_w0[e] < w || (s_w0[e] == w && e < tid)) ? 1 : 0;
-        // Few tiles (the host counts them by capacity; with an uneven router most experts may hold next to nothing): tiles of at
-        // most LIGHT_BLOCKS blocks, twice as many and half as much MFMA work in each, if they fit one round and the plan.
-        // Forward pair, 64 experts of 2048 x 4096, nine with rows, three of them 256 (144 and 72 tiles, now 192 and 96): 147 -> 131 us.
-        // The usual tiles' work still orders the experts, and one round's shares are equal in tile count.
-        if (p.low_tiles > 0) {
-            int tall = 0, low = 0;
-            for (int e = 0; e < p.E; ++e) {
-                tall += s_cnt[e].x;
-                low += s_cnt[e].y;
-            }
-            if (tall * nt <= 5 * p.cus_per_xcd && low * nt <= p.low_tiles && hv > 0) hv = (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS;
+        int r = 0, usual = 0, rest = 0;
+        for (int e = 0; e < p.E; ++e) {
+            r += (s_w0[e] < w || (s_w0[e] == w && e < tid)) ? 1 : 0;
+            usual += s_cnt[e].x;
+            rest += s_cnt[e].y;
         }
+        // Few tiles (the host counts them by capacity; with an uneven router most experts may hold next to nothing): tiles of at
+        // most LIGHT_BLOCKS blocks, twice as many and half as much MFMA work in each, by the rule of kernel_choice.h.  The usual
+        // tiles' work still orders the experts, and one round's shares are equal in tile count.
+        if (hv > 0 && gemm_low_tiles(usual * nt, (rest & 0xfffff) * nt, (rest >> 20) * nt, p.cus_per_xcd, p.low_tiles))
+            hv = (nb + LIGHT_BLOCKS - 1) / LIGHT_BLOCKS;
         const int pos = r < (p.E + 1) / 2 ? 2 * r : 2 * (p.E - 1 - r) + 1;
         s_eid[pos] = tid;
         s_kept[pos] = kx;
@@ -766,7 +764,7 @@ moe_status_t launch_gemm_bf16_plans(const GemmDesc *descs, int n, hipStream_t s)
         p.cus_per_xcd = num_compute_units() / 8 > 0 ? num_compute_units() / 8 : 1;
         if (p.rows_from_kept) {
             const int64_t room = (int64_t)p.E * ((p.M + BM - 1) / BM) * p.nt;          // tiles of the plan buffer
-            p.low_tiles = (int)(room < 8 * p.cus_per_xcd ? room : 8 * p.cus_per_xcd);
+            p.low_tiles = (int)(room < 8 * p.cus_per_xcd ? room : 8 * p.cus_per_xcd);  // more never fit one round
         }
     }
     if (np == 0) return MOE_OK;

@@ -19,6 +19,7 @@ bool gemm_rows_chosen_(int64_t E, int64_t M, int64_t N) { return gemm_rows_chose
 int gemm_rows_blocks_(int64_t M) { return gemm_rows_blocks(M); }
 int64_t gemm_rows_tiles_(int64_t E, int64_t M, int64_t N, int blocks) { return gemm_rows_tiles(E, M, N, blocks); }
 bool gemm_rows_lone_(int64_t tiles, int blocks, bool b_xc) { return gemm_rows_lone(tiles, blocks, b_xc); }
+bool gemm_low_tiles_(int usual, int low, int light, int units, int room) { return gemm_low_tiles(usual, low, light, units, room); }
 bool gemm_wgrad_chosen_(int64_t E, int64_t M, int64_t N, int64_t K, bool whole) { return gemm_wgrad_chosen(E, M, N, K, whole); }
 int gemm_wgrad_run_(int64_t E, int64_t M, int64_t N) { return gemm_wgrad_run(E, M, N); }
 bool gemm_panel_chosen_(int64_t E, int64_t M, int64_t N, int64_t K) { return gemm_panel_chosen(E, M, N, K); }
@@ -39,6 +40,7 @@ SIGNATURES = {
     "adamw_launch_len": (I64, [I64]), "adamw_blocks": (I64, [I64]), "adamw_threads": (INT, []),
     "adamw_streams": (BOOL, [I64, BOOL]), "gemm_rows_chosen": (BOOL, [I64, I64, I64]), "gemm_rows_blocks": (INT, [I64]),
     "gemm_rows_tiles": (I64, [I64, I64, I64, INT]), "gemm_rows_lone": (BOOL, [I64, INT, BOOL]),
+    "gemm_low_tiles": (BOOL, [INT, INT, INT, INT, INT]),
     "gemm_wgrad_chosen": (BOOL, [I64, I64, I64, I64, BOOL]), "gemm_wgrad_run": (INT, [I64, I64, I64]),
     "gemm_panel_chosen": (BOOL, [I64, I64, I64, I64]), "gemm_panel_run": (INT, [I64, I64, I64, I64]),
     "gemm_panel_fills": (BOOL, [I64, I64, I64, I64]), "f32_plan": (INT, [I64, I64, I64, I64]),
@@ -63,6 +65,13 @@ class Rules:
             return "large"
         b = self.gemm_rows_blocks(C)
         return ("rows", b, bool(self.gemm_rows_lone(self.gemm_rows_tiles(E, C, N, b), b, forward)))
+
+    def low_tiles(self, rows, N):
+        """Whether the large kernel's plan cuts these experts' rows into low tiles (256 compute units in 8 XCDs)"""
+        nt, nb = -(-N // 256), [-(-n // 32) for n in rows]
+        low, light = sum(-(-b // 4) for b in nb if b > 4), sum(0 < b <= 4 for b in nb)
+        usual = sum(1 if b <= 4 else -(-b // 9) for b in nb if b)
+        return low > 0 and bool(self.gemm_low_tiles(usual * nt, low * nt, light * nt, 32, min(len(rows) * -(-max(rows) // 256) * nt, 256)))
 
     def weight_gemm(self, E, C, M, N, aligned=True):
         """Kernel of a weight gradient [M, N] over C rows where the panel kernel does not come first: 'large', or ('wgrad', whole

@@ -27,7 +27,8 @@ LARGE = [
     (256, (289, 320, 300, 352, 384, 400, 161), 72, 136),               # two tiles: five and five blocks to seven and six
     (256, (545, 576, 512, 513, 450, 31), 136, 192),                    # two tall tiles; eight and nine blocks; odd and even k-tiles
     (256, (800, 161, 177), 200, 264),                                  # nine, eight and eight blocks; a second column tile of 8
-    (64, (170, 161, 190, 64, 150), 520, 776),                          # ragged column tiles, many k-tiles; weight gradients too
+    (64, (170, 161, 190, 64, 150), 520, 776),                          # ragged column tiles, many k-tiles; low tiles in GEMM2 and dD; weight gradients too
+    (128, (170, 161, 190, 64, 150), 520, 776),                         # the same without low tiles
 ]
 
 
@@ -36,9 +37,11 @@ LARGE = [
 def test_large_kernel(orc, E, rows, h, f, act):
     k = choice().layer_gemms(E, max(rows), h, f)
     assert all(k[g] == "large" for g in ("fwd1", "fwd2", "dh", "dd")), k
-    if E == 64:
+    if E <= 128:
         assert k["dw1"] == "large" and k["dw2"] == "large", k
-    run_rows(orc, spread(E, rows), h, f, act, per_expert=True)
+    rows = spread(E, rows)
+    assert not choice().low_tiles(rows, f) and choice().low_tiles(rows, h) == (E == 64)
+    run_rows(orc, rows, h, f, act, per_expert=True)
 
 
 @pytest.mark.parametrize("E,rows,h,f,kernels", [
@@ -65,7 +68,8 @@ def test_few_row_kernels(orc, E, rows, h, f, kernels):
     run_rows(orc, few, h, f, per_expert=True)
 
 
-@pytest.mark.parametrize("E,rows,h,f", [(256, (161, 288, 0, 300, 256, 130), 136, 72), (64, (170, 161, 190, 64, 0, 150), 520, 776)])
+@pytest.mark.parametrize("E,rows,h,f", [
+    (256, (161, 288, 0, 300, 256, 130), 136, 72), (64, (170, 161, 190, 64, 0, 150), 520, 776), (128, (170, 161, 190, 64, 0, 150), 520, 776)])
 def test_folded_permutations_on_the_large_kernel(E, rows, h, f):
     """Dispatch read through the index by the first GEMM and combine written by the second, on the large kernel's light,
     partial, full and tall tiles: the same bits as the separate passes."""

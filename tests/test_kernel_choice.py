@@ -52,6 +52,16 @@ def test_form_of_the_row_kernel(rules, tiles, blocks, forward, lone):
     assert rules.gemm_rows_lone(tiles, blocks, forward) == lone
 
 
+@pytest.mark.parametrize("usual,low,light,room,fits", [
+    (128, 256, 0, 256, True), (129, 257, 0, 512, False), (160, 192, 64, 256, True), (161, 192, 64, 256, False), (128, 252, 4, 256, False),
+    (128, 248, 8, 256, True), (128, 248, 9, 512, False), (130, 245, 10, 256, False), (28, 40, 8, 48, True), (28, 40, 8, 47, False)])
+def test_low_tiles_fit_one_round_of_every_xcd(rules, usual, low, light, room, fits):
+    """An XCD works off its eighths of the two lists by itself: what fits 256 units need not fit the 32 of each."""
+    assert rules.gemm_low_tiles(usual, low, light, 32, room) == fits
+    if fits:
+        assert max(((x + 1) * low >> 3) - (x * low >> 3) + ((x + 1) * light >> 3) - (x * light >> 3) for x in range(8)) <= 32
+
+
 def test_kernels_of_layers_at_the_lines(rules):
     """Which kernel serves a layer's GEMMs on both sides of each line"""
     assert rules.row_gemm(64, 160, 2048, True) == ("rows", 5, False) and rules.row_gemm(64, 161, 2048, True) == "large"
