@@ -1,7 +1,7 @@
 """The block form of the fp32 grouped GEMM (tiles of up to 160 x 64 on 16 x 16 x 4 MFMAs) at the edges of its tiles, against
-the CPU oracle; tolerance as for every fp32 parity test (1e-5 per row and tile).  Experts hold no rows or at least six: a row of d_w2
-is a sum over the expert's rows of hact times d_y, and where a single hact is next to zero (its z is a sum of 512 products with a
-rounding error of 1e-7, whatever computes it) that row's own norm measures nothing."""
+the CPU oracle; tolerance as for every fp32 parity test (1e-5 per row and tile).  In the first test experts hold no rows or at least
+six: a row of d_w2 is a sum over the expert's rows of hact times d_y, and where a single hact is next to zero (its z is a sum of 512
+products with a rounding error of 1e-7, whatever computes it) that row's own norm measures nothing."""
 import pytest
 import torch
 
@@ -26,7 +26,7 @@ def fill(E, rows, rest):
 @pytest.mark.parametrize("E,rows,h,f,want,wgrad", [
     # one tile per unit, five blocks: ragged columns and k-tiles; 8 to 10 and 16 to 20 row blocks
     (8, (320, 272, 257, 256, 241, 240, 160, 161), 1024, 1020, [(5, True), (5, True)], BLOCK),
-    # two workgroups per unit; experts without rows, with one, with partial blocks
+    # two workgroups per unit; experts without rows, with a handful, with partial blocks
     (64, fill(64, (160, 161, 320, 0, 6, 15, 16, 17, 33, 0), (130, 128, 97)), 512, 516, [(3, False), (5, False)], WIDE),
     # three and two blocks
     (8, (140, 128, 129, 127, 112, 96, 150, 142), 1024, 1024, [(3, True), (3, True)], WIDE),
@@ -43,6 +43,17 @@ def fill(E, rows, rest):
 def test_block_form(orc, E, rows, h, f, want, wgrad):
     assert forms(E, rows, h, f) == (want, wgrad)
     run_rows(orc, rows, h, f, dtype="f32")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("E,rows,h,f,want,wgrad", [
+    (128, fill(128, (1, 2, 3, 4, 5, 0), (1, 5, 2)), 260, 260, [(5, False), (5, False)], WIDE),
+    # weight gradients whose only k-tile holds one to five rows, beside long ones
+    (8, (900, 1, 2, 5, 0, 3, 700, 4), 516, 516, [(3, True), (3, True)], BLOCK),
+])
+def test_block_form_of_handfuls(orc, E, rows, h, f, want, wgrad):
+    assert forms(E, rows, h, f) == (want, wgrad)
+    run_rows(orc, rows, h, f, dtype="f32", few=True)
 
 
 def test_estimates_never_ask_for_a_second_round_alone():

@@ -103,3 +103,51 @@ def test_large_gemm_loops_do_not_spill(kernels):
                 assert not re.match(r"s_waitcnt vmcnt\(0\)", l), (name, l)
         assert mfma >= 128, name          # the loops were found
     assert found == 5
+
+
+def waits(lines):
+    """Counts of the explicit waits: outstanding global accesses, no LDS access"""
+    return {int(n) for l in lines for n in re.findall(r"^s_waitcnt vmcnt\((\d+)\) lgkmcnt\(0\)$", l)}
+
+
+def test_panel_kernel_counts_loads_and_stores(kernels):
+    """gemm_panel_kernel waits for a tile with the loads of S - 2 newer tiles (NKS each) and, once that many have been written,
+    the 16 stores of S - 1 older ones outstanding; B's panel is waited for behind the first tiles' loads where it lies beside
+    the ring.  Every tile issues its 16 stores (8 in the code of a half tile), nothing is spilled, and the private staging is
+    ordered as in gemm_wgrad_kernel."""
+    found = 0
+    for name, lines in kernels("gemm_panel.hip").items():
+        m = re.search(r"gemm_panel_kernelILi(\d+)E", name)
+        if not m:
+            continue
+        found += 1
+        want = {0}
+        for nks in range(1, int(m[1]) + 1):
+            s = min(4, 16 // nks)
+            want |= {(s - 2) * nks, (s - 2) * nks + (s - 1) * 16, (s - 1) * nks if (s + 4) * nks <= 20 else 0}
+        assert waits(lines) == want, (name, want, waits(lines))
+        assert sum(l.startswith("buffer_store_dwordx4") for l in lines) == 8 * int(m[1]), name
+        assert not any(l.startswith("scratch_") for l in lines), name
+        ev = ["W" if l.startswith("ds_write") else "R" if l.startswith("ds_read_b128") else "B" for l in lines
+              if l.startswith(("ds_write", "ds_read_b128")) or "wave barrier" in l]
+        assert "W" in ev and "R" in ev, name
+        for a, b in zip(ev, ev[1:]):
+            assert a == b or "B" in (a, b), (name, "".join(ev))
+    assert found == 2
+
+
+def test_f32_block_kernel_keeps_its_ring_in_flight(kernels):
+    """gemm_f32_block_kernel waits for a k-tile with S - 2 newer ones outstanding: one load of B per wave and its share of the 4 MB
+    chunks of A; nothing is spilled."""
+    seen = set()
+    for name, lines in kernels("gemm_f32.hip").items():
+        m = re.search(r"gemm_f32_block_kernelILi\d+ELb([01])ELb[01]ELi(\d+)ELb([01])E", name)
+        if not m:
+            continue
+        axc, mb, lone = m[1] == "1", int(m[2]), m[3] == "1"
+        stages = {5: 4, 3: 5, 2: 6}[mb] if lone else 2
+        per_wave = {1 + len(range(w, 4 * mb, 8)) for w in range(8)}
+        assert waits(lines) == {0} | {(stages - 2) * n for n in per_wave}, (name, waits(lines))
+        assert not any(l.startswith("scratch_") for l in lines), name
+        seen.add((axc, mb, lone))
+    assert seen == {(False, mb, d) for mb in (2, 3, 5) for d in (False, True)} | {(True, 2, False)}
