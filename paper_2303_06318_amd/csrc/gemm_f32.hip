@@ -390,7 +390,7 @@ static void launch_f32(const GemmDesc &d, hipStream_t s) {
             default: return launch_f32_tiles<EPI, AXC, BXC, false>(d, s);
         }
     } else {
-        const F32Plan p = f32_row_plan(d.E, d.M, d.rows, d.N, d.K);
+        const F32Plan p = f32_row_plan(d.E, d.M, d.rows, d.N, d.K, BXC);
         if (p.mb == 5) launch_f32_block<EPI, AXC, BXC, 5>(d, s, p.lone);
         else if (p.mb == 3) launch_f32_block<EPI, AXC, BXC, 3>(d, s, p.lone);
         else if (p.mb == 2) launch_f32_block<EPI, AXC, BXC, 2>(d, s, p.lone);

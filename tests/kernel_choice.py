@@ -26,7 +26,7 @@ bool gemm_panel_chosen_(int64_t E, int64_t M, int64_t N, int64_t K) { return gem
 int gemm_panel_run_(int64_t E, int64_t M, int64_t N, int64_t K) { return gemm_panel_run(E, M, N, K); }
 bool gemm_panel_fills_(int64_t E, int64_t M, int64_t N, int64_t K) { return gemm_panel_fills(E, M, N, K); }
 int f32_plan_(int64_t E, int64_t R, int64_t N, int64_t K) { const F32Plan p = f32_plan(E, R, N, K); return p.mb * 2 + p.lone; }
-int f32_row_plan_(int64_t E, int64_t M, int64_t R, int64_t N, int64_t K) { const F32Plan p = f32_row_plan(E, M, R, N, K); return p.mb * 4 + p.wide * 2 + p.lone; }
+int f32_row_plan_(int64_t E, int64_t M, int64_t R, int64_t N, int64_t K, bool b_xc) { const F32Plan p = f32_row_plan(E, M, R, N, K, b_xc); return p.mb * 4 + p.wide * 2 + p.lone; }
 int f32_wgrad_form_(int64_t E, int64_t M, int64_t N, int64_t R) { return f32_wgrad_form(E, M, N, R); }
 bool gate_direct_(bool f32, int64_t T) { return gate_direct(f32, T); }
 bool gate_dwg_direct_(bool f32, int64_t T, int E) { return gate_dwg_direct(f32, T, E); }
@@ -44,7 +44,7 @@ SIGNATURES = {
     "gemm_wgrad_chosen": (BOOL, [I64, I64, I64, I64, BOOL]), "gemm_wgrad_run": (INT, [I64, I64, I64]),
     "gemm_panel_chosen": (BOOL, [I64, I64, I64, I64]), "gemm_panel_run": (INT, [I64, I64, I64, I64]),
     "gemm_panel_fills": (BOOL, [I64, I64, I64, I64]), "f32_plan": (INT, [I64, I64, I64, I64]),
-    "f32_row_plan": (INT, [I64, I64, I64, I64, I64]),
+    "f32_row_plan": (INT, [I64, I64, I64, I64, I64, BOOL]),
     "f32_wgrad_form": (INT, [I64, I64, I64, I64]), "gate_direct": (BOOL, [BOOL, I64]), "gate_dwg_direct": (BOOL, [BOOL, I64, INT]),
     "gate_dx_direct": (BOOL, [BOOL, I64, I64, INT, BOOL]), "gate_dx_chunk": (INT, [I64, I64, INT]),
 }

@@ -107,5 +107,5 @@ def test_tile_edges_f32(orc, rows, h, f):
     r, R = choice(), min(-(-sum(rows) // len(rows)), max(rows))
     wide = len(rows) == 32
     assert r.f32_wgrad_form(len(rows), h, f, R) == (1 if wide else 0)
-    assert [r.f32_plan(len(rows), R, n, k) >> 1 for n, k in ((f, h), (h, f))] == [0, 2 if h == 256 else 0]
+    assert [r.f32_row_plan(len(rows), max(rows), R, n, k, True) >> 2 for n, k in ((f, h), (h, f))] == [0, 2 if h == 256 else 0]
     run_rows(orc, rows, h, f, dtype="f32")

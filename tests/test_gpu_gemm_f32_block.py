@@ -13,9 +13,13 @@ NARROW, WIDE, BLOCK = range(3)
 
 
 def forms(E, rows, h, f):
-    """(row blocks of a tile, alone on its unit) of GEMM1 / dH and of GEMM2 / dD, form of the weight gradients"""
-    r, R = choice(), min(-(-sum(rows) // E), max(rows))
-    return [(p >> 1, bool(p & 1)) for p in (r.f32_plan(E, R, f, h), r.f32_plan(E, R, h, f))], r.f32_wgrad_form(E, h, f, R)
+    """(row blocks of a tile, alone on its unit) of GEMM1 and of GEMM2 (from 24 rows on of dH and of dD too), form of the weight
+    gradients"""
+    r, C = choice(), max(rows)
+    R = min(-(-sum(rows) // E), C)
+    a, b = ([r.f32_row_plan(E, C, R, n, k, xc) for n, k in ((f, h), (h, f))] for xc in (True, False))
+    assert a == b or R < 24
+    return [(p >> 2, bool(p & 1)) for p in a], r.f32_wgrad_form(E, h, f, R)
 
 
 def fill(E, rows, rest):
@@ -47,7 +51,8 @@ def test_block_form(orc, E, rows, h, f, want, wgrad):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("E,rows,h,f,want,wgrad", [
-    (128, fill(128, (1, 2, 3, 4, 5, 0), (1, 5, 2)), 260, 260, [(5, False), (5, False)], WIDE),
+    (32, fill(32, (1, 2, 3, 4, 5, 0), (1, 5, 2)), 1024, 1020, [(5, False), (0, False)], WIDE),
+    (128, fill(128, (5, 4, 0, 1), (3, 2)), 220, 292, [(0, False), (5, False)], WIDE),
     # weight gradients whose only k-tile holds one to five rows, beside long ones
     (8, (900, 1, 2, 5, 0, 3, 700, 4), 516, 516, [(3, True), (3, True)], BLOCK),
 ])
@@ -69,8 +74,8 @@ def test_estimates_never_ask_for_a_second_round_alone():
                         assert E * -(-N // 64) * -(-(R // 16 + 1) // (2 * mb)) <= 256
 
 
-def row_form(E, M, R, N, K):
-    v = choice().f32_row_plan(E, M, R, N, K)
+def row_form(E, M, R, N, K, b_xc=True):
+    v = choice().f32_row_plan(E, M, R, N, K, b_xc)
     return "block" if v >> 2 else "wide" if v & 2 else "narrow"
 
 
@@ -91,6 +96,15 @@ def test_every_capacity_has_a_launch():
                         assert tiles < 1 << 22
     assert row_form(128, 2200000, 2200000, 64, 64) == "wide" and row_form(1, 3000000, 100, 64, 64) == "wide"
     assert row_form(1, 2097120, 100, 64, 64) == "narrow" and row_form(1, 2097121, 100, 64, 64) == "wide"
+
+
+@pytest.mark.parametrize("E,R,K,N,forward,backward", [
+    (16, 20, 2048, 2048, "narrow", "narrow"), (64, 16, 1024, 1024, "narrow", "narrow"), (128, 5, 84, 3404, "narrow", "narrow"),
+    (64, 4, 2620, 540, "narrow", "narrow"), (32, 2, 1024, 1020, "block", "narrow"), (64, 6, 1924, 472, "block", "narrow"),
+    (8, 19, 832, 3140, "block", "narrow"), (4, 30, 4096, 4096, "block", "block"), (32, 40, 440, 1912, "block", "block")])
+def test_form_of_few_rows(E, R, K, N, forward, backward):
+    """The faster form of a forward and of a data-gradient GEMM, as measured"""
+    assert (row_form(E, 2 * R, R, N, K), row_form(E, 2 * R, R, N, K, False)) == (forward, backward)
 
 
 @pytest.mark.gpu
