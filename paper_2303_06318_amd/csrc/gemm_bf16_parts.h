@@ -1,6 +1,7 @@
-// Device code shared by the bf16 grouped GEMM kernels: activations of the epilogues, operand loads from global
-// memory straight into LDS, fragment reads.  Both kernels run 512 threads, k-tiles of 64 and the same MFMA with
-// the same operand order, so for the same inputs they add up in the same order and give the same bits.
+// Device code shared by the matrix kernels: activations of the bf16 epilogues, operand loads from global memory straight
+// into LDS, fragment reads.  The bf16 grouped GEMMs (large, few-row, weight gradients, panel) run 512 threads and the same
+// MFMA with the same operand order over k ascending, so for the same inputs they add up in the same order and give the same
+// bits; the gate of long token tensors and the fp32 block form use the loaders and the fragment reads.
 #pragma once
 #include "moe_common.h"
 

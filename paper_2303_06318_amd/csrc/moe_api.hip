@@ -235,11 +235,12 @@ static SideStream *side_stream(hipStream_t caller) {
 // When the backward's GEMMs stay on the caller's stream: two streams cost about 15 us of events, and where every
 // GEMM is bound by the weights' traffic and fills the chip, running two at once only mixes reads with writes.
 // Whole expert backward, one stream / two:
-//   few rows:       16 experts x 48 rows, 4096 x 4096: 426 / 461 us; 64 x 6 rows, 2048 x 2048: 412 / 435 (100 rows: 605 / 561)
-//   small weights:  32 x 100 rows, 1024 x 1024: 70 / 79; 4 x 6 rows, 2048 x 2048: 43 / 58; 8 x 100 rows, 1024 x 4096: 90 / 91
-//                   (200 rows: 107 / 104)
-// and only where the weight gradients have a kernel for few rows (32 x 60 rows, 2768 x 1096, without: 280 / 254).  From
-// panels (gemm_panel.hip) also up to 160 rows, where their workgroups fill the chip to the end.
+//   few rows:       16 experts x 48 rows, 4096 x 4096: 408 / 426 us; 64 x 6 rows, 2048 x 2048: 391 / 409
+//   small weights:  32 x 100 rows, 1024 x 1024: 67 / 79; 4 x 6 rows, 2048 x 2048: 38 / 66; 256 x 48 rows, 512 x 512: 127 / 132
+//                   (8 x 200 rows, 1024 x 4096: 101 / 97)
+// and only where the weight gradients have a kernel for few rows (32 x 60 rows, 2768 x 1096, without: 268 / 261).  From
+// panels (gemm_panel.hip) also up to 160 rows, where their workgroups fill the chip to the end (64 x 100 rows, 2048 x 2048:
+// 504 / 518; 16 x 128 rows, 4160 x 2112, which do not: 305 / 279).
 static bool bwd_one_stream(const moe_shape_t &s, const GemmDesc &dw2, const GemmDesc &dw1) {
     if (gemm_panel_fits(dw2) && gemm_panel_fits(dw1) && s.C <= 160)
         return s.C <= 64 || (gemm_panel_fills(s.E, dw2.M, dw2.N, dw2.K) && gemm_panel_fills(s.E, dw1.M, dw1.N, dw1.K));

@@ -60,6 +60,9 @@ def test_rule_of_the_panel_kernel():
     # the other gradient's rows are parts of lines: few experts and results, many
     (16, 2256, 1280, (16, 64, 144), (161, 200)), (4, 1616, 5440, (16, 40, 64, 144), (200,)),
     (32, 1200, 1984, (), (16, 64, 144)), (32, 920, 1216, (), (16, 64, 130)), (16, 3000, 1600, (), (6, 64, 160)),
+    # 65 to 160 rows of few experts: few results, many, and a whole round
+    (8, 1536, 2752, (100, 144), (16, 64, 161)), (4, 2624, 3904, (100, 130, 150), (64, 200)), (2, 4544, 4928, (100, 150), ()),
+    (8, 2816, 2112, (), (100, 150)), (16, 1472, 1472, (), (100, 150)), (4, 2048, 4096, (), (100, 160)),
     (8, 2048, 2048, (), (6, 64, 160)), (64, 1024, 1024, (), (6, 64, 128))])
 def test_sizes_at_which_the_panel_kernel_was_measured(E, M, N, slower, faster):
     """Row counts at which it was slower and faster than the kernel that serves otherwise"""
